@@ -729,7 +729,6 @@ int chem_set_mechanism(chem_ctx *c, const chem_mech_desc *m) {
     M.off_e = off; off += N;
     M.off_cp = off; off += N;
     M.off_tb = off; off += M.n;
-    M.off_sv = off; off += 128;   // triangular-solve results, by pivot step (2 x 64)
     M.lds_doubles = off;
     {
         std::vector<MechDev> one(1, M);

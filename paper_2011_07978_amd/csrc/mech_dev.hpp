@@ -127,7 +127,7 @@ struct MechDev {
     int has_fo;             // any fall-off or PLOG reaction
     // per-wavefront LDS region (offsets in doubles); the Jacobian (n rows of
     // stride ldj) has a slot of its own
-    int off_q, off_C, off_g, off_gi, off_h, off_e, off_cp, off_tb, off_sv, lds_doubles;
+    int off_q, off_C, off_g, off_gi, off_h, off_e, off_cp, off_tb, lds_doubles;
 };
 
 struct IntParams {
