@@ -16,6 +16,9 @@ SOURCES = ["api.cpp", "balance.cpp", "integrate.hip", "integrate_fo.hip", "integ
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
           # packed FP32 instructions are kept out of every kernel
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # the register-resident matrices need every loop over them unrolled;
+          # for 64 rows that exceeds the default size limit of #pragma unroll
+          "-mllvm", "-pragma-unroll-threshold=100000",
           "-Wno-unused-command-line-argument", "-Wno-unused-result"]
 
 

@@ -39,11 +39,11 @@ size_t big_lds_bytes(int n);
 hipError_t big_prepare(int n);
 int big_occupancy(int n);
 hipError_t launch_integrate_big(const MechDev &M, const MechDev *Md, const IntParams &P,
-                                int schedule, int grid, double *jws, hipStream_t s);
+                                int schedule, int grid, hipStream_t s);
 hipError_t launch_big_rhs_jac(const MechDev &M, const MechDev *Md, const IntParams &P, double *f,
                               double *J, hipStream_t s);
 hipError_t launch_big_rodas_step(const MechDev &M, const MechDev *Md, const IntParams &P, double h,
-                                 double *ynew, double *err, double *jws, hipStream_t s);
+                                 double *ynew, double *err, hipStream_t s);
 hipError_t launch_map_scatter(int64_t ncells, int N, double *T, double *Y, const uint8_t *flags,
                               const int64_t *ref, const double *snap, double *delta,
                               const double *nasa_t, const double *invW, uint8_t *status,
@@ -86,7 +86,6 @@ struct chem_ctx {
     // large mechanisms (n > 64): workgroup-per-cell kernel, Jacobian slots of
     // the workgroups in flight
     bool big = false;
-    double *d_jws = nullptr;
     int big_slots = 0;
     bool in_capture = false, capture_failed = false;   // chem_graph_begin .. _end
     Surrogate *sur = nullptr;                // learned surrogate (null: not available)
@@ -218,8 +217,6 @@ static void free_mech(chem_ctx *c) {
     if (c->d_mapw) (void)hipFree(c->d_mapw);
     if (c->d_snap) (void)hipFree(c->d_snap);
     if (c->d_delta) (void)hipFree(c->d_delta);
-    if (c->d_jws) (void)hipFree(c->d_jws);
-    c->d_jws = nullptr;
     c->big = false;
     c->big_slots = 0;
     c->d_mapw = c->d_snap = c->d_delta = nullptr;
@@ -756,11 +753,6 @@ int chem_set_mechanism(chem_ctx *c, const chem_mech_desc *m) {
                 c->big = true;
                 c->occ = occ;
                 c->big_slots = c->num_cu * occ;
-                const size_t bytes = sizeof(double) * (size_t)M.n * M.n * c->big_slots;
-                if (hipMalloc((void **)&c->d_jws, bytes) != hipSuccess) {
-                    free_mech(c);
-                    return fail(c, CHEM_E_OOM, "hipMalloc Jacobian slots (%zu bytes)", bytes);
-                }
             }
         }
     }
@@ -964,7 +956,7 @@ static int integrate_core(chem_ctx *c, int64_t n, double *T, const double *p, do
         }
         if (stats) HIPCHK(c, hipEventRecord(c->ev2, s));
         if (c->big)
-            HIPCHK(c, launch_integrate_big(c->M, c->d_mech, P, c->opt.schedule, grid, c->d_jws, s));
+            HIPCHK(c, launch_integrate_big(c->M, c->d_mech, P, c->opt.schedule, grid, s));
         else
             HIPCHK(c, launch_integrate(c->NP, c->M, c->d_mech, P, c->opt.schedule, grid, s));
         if (stats) HIPCHK(c, hipEventRecord(c->ev3, s));
@@ -1237,15 +1229,9 @@ int chem_rodas_step(chem_ctx *c, int64_t n, const double *T, const double *p, co
     P.ncells = n;
     P.T = const_cast<double *>(T); P.p = p; P.Y = const_cast<double *>(Y);
     if (c->big) {
-        // one Jacobian slot per cell for this check
-        if (capturing(c)) return fail(c, CHEM_E_CAPTURE_UNSAFE, "chem_rodas_step allocates here");
-        double *jws = nullptr;
-        const size_t bytes = sizeof(double) * (size_t)c->M.n * c->M.n * (size_t)n;
-        if (hipMalloc((void **)&jws, bytes) != hipSuccess)
-            return fail(c, CHEM_E_OOM, "hipMalloc Jacobian slots (%zu bytes)", bytes);
-        hipError_t e = launch_big_rodas_step(c->M, c->d_mech, P, h, ynew, err, jws, c->stream);
+        if (capturing(c)) return fail(c, CHEM_E_CAPTURE_UNSAFE, "chem_rodas_step synchronises here");
+        hipError_t e = launch_big_rodas_step(c->M, c->d_mech, P, h, ynew, err, c->stream);
         if (e == hipSuccess) e = c->stream ? hipStreamSynchronize(c->stream) : hipDeviceSynchronize();
-        (void)hipFree(jws);
         if (e != hipSuccess) return fail(c, CHEM_E_HIP, "big rodas step: %s", hipGetErrorString(e));
         return CHEM_OK;
     }

@@ -1,21 +1,25 @@
 // Per-cell stiff chemistry integration for large mechanisms (64 < n <= ~138
 // unknowns), FP64, gfx950.
 //
-// A workgroup of four wavefronts owns one cell; thread i holds unknown i of
-// y = (T, Y_1..Y_N).  The iteration matrix M = I/(gamma h) - J (n x n) lives
-// in LDS (up to ~150 KB, so one cell per CU); the Jacobian is kept for reuse
-// after a rejected step in a global workspace that exists only for the
-// workgroups in flight (one slot per persistent workgroup), not per cell.
+// A workgroup of eight wavefronts owns one cell; threads 2i and 2i + 1 hold
+// unknown i of y = (T, Y_1..Y_N).  The iteration matrix M = I/(gamma h) - J
+// (n x n) lives in LDS (up to ~150 KB, so one cell per CU for the largest
+// mechanisms).
 //   - right-hand side and analytic Jacobian: the formulas of the wavefront
-//     kernel, reaction pass over 256 threads with LDS float atomics issued one
-//     wavefront at a time, block reductions combined in a fixed order, so the
-//     result does not depend on scheduling;
-//   - LU with partial pivoting, right-looking and blocked by 16 columns: each
-//     panel is factored column by column (rows swapped in place), the block
-//     row of U by a forward substitution, and the trailing submatrix updated
-//     on the FP64 matrix cores (v_mfma_f64_16x16x4f64);
-//   - triangular solves blocked by 16 rows: one wavefront solves each
-//     diagonal block, then every thread updates its row.
+//     kernel, reaction pass over all threads.  Production rates are summed
+//     with LDS float atomics into one array per wavefront (as many as the LDS
+//     holds) added in a fixed order; the Jacobian's scatter is issued one
+//     wavefront at a time; block reductions combine in a fixed order, so the
+//     result does not depend on scheduling.  The Jacobian is assembled in the
+//     matrix's place and turned into M there; after a rejected step it is
+//     assembled again (the same y gives the same bits), which happens for
+//     about 1 % of the steps and costs less than keeping a copy for all;
+//   - block Gauss-Jordan elimination with partial pivoting, 16 columns at a
+//     time: one wavefront inverts the panel's pivot block in registers while
+//     the others update the columns behind the next panel on the FP64 matrix
+//     cores (v_mfma_f64_16x16x4f64);
+//   - a stage's solve is one pass over the panels (nine steps for 131
+//     unknowns) and a product with the inverted pivot blocks.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include "mech_dev.hpp"
@@ -25,9 +29,13 @@ namespace chem {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BT = 256;   // threads per cell
-constexpr int NB = 16;    // LU block
-constexpr int SB = 16;    // triangular-solve block
+// Eight wavefronts, two per SIMD: the reaction pass and the trailing updates
+// have twice the wavefronts of a four-wavefront group to hide their latencies
+// with.
+constexpr int BT = 512;
+constexpr int NW = BT / 64;
+constexpr int NB = 16;    // panel width: four K = 4 matrix-core steps
+constexpr size_t kBigLds = 160 * 1024;   // LDS of a CU
 
 __constant__ double kBigA[6][6] = {
     {0, 0, 0, 0, 0, 0},
@@ -53,15 +61,27 @@ __device__ __forceinline__ void lds_add_b(double *p, double v) {
 // LDS layout of one cell (in doubles); lda is odd so that thread-per-row
 // accesses fall into distinct banks.
 struct BigLds {
-    int n, N, lda;
-    double *A, *C, *g, *hh, *e, *cp, *tb, *w, *vec, *red;
-    int *ipiv, *perm;
+    int n, N, lda, nw;   // nw: copies of the production-rate array
+    double *A, *C, *g, *gi, *hh, *e, *cp, *tb, *w, *red;
+    int *step, *prow;    // row -> elimination step, step -> pivot row
 };
 
+constexpr int kRedDoubles = 48;
 __host__ __device__ inline int big_lda(int n) { return n | 1; }
-__host__ __device__ inline size_t big_lds_doubles(int n) {
+// everything but the copies of the production rates past the first
+__host__ __device__ inline size_t big_base_doubles(int n) {
     const int N = n - 1;
-    return (size_t)n * big_lda(n) + 4 * (N + 1) + 2 * N + n + n + 16 + n;  // ipiv, perm share n doubles
+    return (size_t)n * big_lda(n) + 5 * (N + 1) + 2 * N + n + kRedDoubles + n;  // step, prow share n doubles
+}
+// One production-rate array per wavefront where the LDS holds them (up to 135
+// unknowns); fewer are shared by wavefronts taking turns.
+__host__ __device__ inline int big_rate_copies(int n) {
+    int c = NW;
+    while (c > 1 && (big_base_doubles(n) + (size_t)(c - 1) * n) * sizeof(double) > kBigLds) c /= 2;
+    return c;
+}
+__host__ __device__ inline size_t big_lds_doubles(int n) {
+    return big_base_doubles(n) + (size_t)(big_rate_copies(n) - 1) * n;
 }
 
 __device__ __forceinline__ BigLds big_layout(int n, double *lds) {
@@ -69,109 +89,160 @@ __device__ __forceinline__ BigLds big_layout(int n, double *lds) {
     L.n = n;
     L.N = n - 1;
     L.lda = big_lda(n);
+    L.nw = big_rate_copies(n);
     double *q = lds;
     L.A = q; q += (size_t)n * L.lda;
     L.C = q; q += L.N + 1;
     L.g = q; q += L.N + 1;
+    L.gi = q; q += L.N + 1;
     L.hh = q; q += L.N + 1;
-    L.w = q; q += L.N + 1;
     L.e = q; q += L.N;
     L.cp = q; q += L.N;
     L.tb = q; q += n;
-    L.vec = q; q += n;
-    L.red = q; q += 16;
-    L.ipiv = (int *)q;          // n ints
-    L.perm = L.ipiv + n;        // n ints (2n ints fit in n doubles)
+    L.red = q; q += kRedDoubles;
+    L.step = (int *)q;          // n ints
+    L.prow = L.step + n;        // n ints (2n ints fit in n doubles)
+    q += n;
+    L.w = q;                    // nw x (N + 1)
     return L;
 }
 
-// Sum / max over the 256 threads; every thread returns the same bits.
-__device__ __forceinline__ double block_sum(double v, double *red) {
-    const double s = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
+__device__ __forceinline__ int opaque_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
 }
+
+// Max over the workgroup; every thread returns the same bits.
 __device__ __forceinline__ double block_max(double v, double *red) {
     const double s = wave_max(v);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[4 + (threadIdx.x >> 6)] = s;
+    if ((threadIdx.x & 63) == 0) red[36 + (threadIdx.x >> 6)] = s;
     __syncthreads();
-    return max2(max2(red[4], red[5]), max2(red[6], red[7]));
+    double m = red[36];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) m = max2(m, red[36 + i]);
+    return m;
 }
 __device__ __forceinline__ bool block_any(bool p, double *red) {
     return block_max(p ? 1.0 : 0.0, red) > 0.0;
 }
-// value of thread `src` to every thread
-__device__ __forceinline__ double block_bcast(double v, int src, double *red) {
-    __syncthreads();
-    if ((int)threadIdx.x == src) red[8] = v;
-    __syncthreads();
-    return red[8];
+// Wavefront partial sums of quantity i into red[8 i ..]; after a barrier
+// block_total adds them in order.
+__device__ __forceinline__ void block_part(double v, int i, double *red) {
+    const double s = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[NW * i + (threadIdx.x >> 6)] = s;
+}
+__device__ __forceinline__ double block_total(int i, const double *red) {
+    const double *r = red + NW * i;
+    return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
+}
+
+// NASA-7 coefficients and molar mass of the thread's species, kept in
+// registers for the whole launch.
+struct Species {
+    double a1, a2, a3, a4, a5, a6, a7, h2, h3, h4, h5, s3, s4, s5, W, iW;
+};
+__device__ __forceinline__ Species load_species(const MechDev *__restrict__ M) {
+    const int own = threadIdx.x >> 1;
+    const int k = own >= 1 && own <= M->N ? own - 1 : 0;
+    const auto *a = gbl(M->spc) + k * SPC_STRIDE;
+    return {a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13], a[14], a[15]};
+}
+
+__device__ __forceinline__ RxnRec load_rxn(const RxnRec *__restrict__ rxn, int j) {
+    const auto *r = gbl(rxn) + j;
+    RxnRec o;
+    o.lnA = r->lnA; o.b = r->b; o.EaR = r->EaR;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) o.eff[i] = r->eff[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o.idx[i] = r->idx[i];
+    return o;
 }
 
 // -----------------------------------------------------------------------------
-// f(y) and, with JAC, the analytic Jacobian into L.A (row-major, stride lda).
-// Thread i returns f_i.  Same formulas as the wavefront kernel.
+// f(y) and, with JAC, the analytic Jacobian into L.A (row-major, stride lda),
+// or with MAT the iteration matrix diag I - J.  Threads 2i, 2i + 1 return f_i.
+// Same formulas as the wavefront kernel.
 // -----------------------------------------------------------------------------
-template <bool JAC>
-__device__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const double y,
-                          const BigLds &L) {
+template <bool JAC, bool MAT>
+__device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const double y,
+                                          const Species &S, const double diag, const BigLds &L) {
+    // The opaque thread index and sizes keep the addresses and trip counts
+    // derived from them local to this call instead of held (spilled) across
+    // the step loop; so below.
+    asm volatile("" ::: "memory");
     const MechDev &M = *Mp;
-    const int tid = threadIdx.x;
-    const int N = M.N, R = M.R, n = M.n, lda = L.lda;
-    const double T = block_bcast(y, 0, L.red);
+    const int tid = opaque_tid(), own = tid >> 1, half = tid & 1, wv = uniform_i(tid >> 6);
+    int N = M.N, R = M.R, n = M.n;
+    asm volatile("" : "+s"(N), "+s"(R), "+s"(n));
+    const int lda = big_lda(n);
+    const bool sp = own >= 1 && own <= N;
+    const int k = sp ? own - 1 : 0;
+    // the first reaction record is on its way while the thermo runs
+    RxnRec next = load_rxn(M.rxn, tid < R ? tid : R - 1);
+
+    const double yw = sp ? y * S.iW : 0.0;
+    block_part(half == 0 ? yw : 0.0, 0, L.red);
+    if (tid == 0) L.red[32] = y;
+    __syncthreads();
+    const double T = L.red[32];
+    const double sumYW = block_total(0, L.red);
     const double lnT = log(T);
+    const double ln_patm_RT = kLnPatmRu - lnT;
     const double invT = 1.0 / T;
-    const bool sp = tid >= 1 && tid <= N;
-    const int k = sp ? tid - 1 : 0;
-    double cpR = 0.0, hRT = 0.0, gRT = 0.0, dcpR = 0.0, invWk = 0.0, Wk = 0.0;
-    if (sp) {
-        const auto *a = gbl(M.spc) + k * SPC_STRIDE;
-        const double a1 = a[0], a2 = a[1], a3 = a[2], a4 = a[3], a5 = a[4], a6 = a[5], a7 = a[6];
-        const double h2 = a[7], h3 = a[8], h4 = a[9], h5 = a[10];
-        const double s3 = a[11], s4 = a[12], s5 = a[13];
-        cpR = a1 + T * (a2 + T * (a3 + T * (a4 + T * a5)));
-        hRT = a1 + T * (h2 + T * (h3 + T * (h4 + T * h5))) + a6 * invT;
-        const double sR = a1 * lnT + T * (a2 + T * (s3 + T * (s4 + T * s5))) + a7;
-        gRT = hRT - sR;
-        if (JAC) dcpR = a2 + T * (2.0 * a3 + T * (3.0 * a4 + T * (4.0 * a5)));
-        Wk = a[14];
-        invWk = a[15];
-    }
-    const double yw = sp ? y * invWk : 0.0;
-    const double sumYW = block_sum(yw, L.red);
+    const double irho = (RU_ERG * T * sumYW) / p;
     const double rho = p / (RU_ERG * T * sumYW);
     const double Ctot = rho * sumYW;
+    double cpR = 0.0, hRT = 0.0, dcpR = 0.0;
     if (sp) {
-        L.C[k] = rho * yw;
-        L.g[k] = gRT;
-        if (JAC) {
-            L.hh[k] = hRT;
-            L.e[k] = hRT * invWk;
-            L.cp[k] = cpR * invWk;
+        cpR = S.a1 + T * (S.a2 + T * (S.a3 + T * (S.a4 + T * S.a5)));
+        hRT = S.a1 + T * (S.h2 + T * (S.h3 + T * (S.h4 + T * S.h5))) + S.a6 * invT;
+        const double sR = S.a1 * lnT + T * (S.a2 + T * (S.s3 + T * (S.s4 + T * S.s5))) + S.a7;
+        if (JAC) dcpR = S.a2 + T * (2.0 * S.a3 + T * (3.0 * S.a4 + T * (4.0 * S.a5)));
+        // species factor of the equilibrium constants on one thread of the
+        // pair, its reciprocal on the other
+        const double gx = hRT - sR - ln_patm_RT;
+        const double ex = exp(half ? -gx : gx);
+        if (half) {
+            L.gi[k] = ex;
+            if (JAC) {
+                L.e[k] = hRT * S.iW;
+                L.cp[k] = cpR * S.iW;
+            }
+        } else {
+            L.g[k] = ex;
+            L.C[k] = rho * yw;
+            if (JAC) L.hh[k] = hRT;
         }
     }
-    if (tid <= N) L.w[tid] = 0.0;
+    if (tid == 0) {   // the sentinel of missing slots
+        L.C[N] = 1.0;
+        L.g[N] = 1.0;
+        L.gi[N] = 1.0;
+        if (JAC) L.hh[N] = 0.0;
+    }
+    for (int i = tid; i < L.nw * (N + 1); i += BT) L.w[i] = 0.0;
     if (JAC) {
         for (int i = tid; i < n * lda; i += BT) L.A[i] = 0.0;
         if (tid < n) L.tb[tid] = 0.0;
     }
     __syncthreads();
 
-    const double ln_patm_RT = log(P_ATM / (RU_ERG * T));
-    const double lnp = log(p);
-    const auto *rxn = gbl(M.rxn);
-    double *Cl = L.C, *gl = L.g, *hl = L.hh, *wl = L.w, *Jl = L.A, *tbl = L.tb;
-    // Reactions j0 + tid are evaluated by all four wavefronts at once; their
-    // LDS float-atomic scatter is done one wavefront after the other, so the
-    // order of every sum (and the result) does not depend on scheduling.
-    const int wv = tid >> 6;
+    const double lnp = M.has_fo ? log(p) : 0.0;
+    double *Cl = L.C, *gl = L.g, *gil = L.gi, *hl = L.hh, *Jl = L.A, *tbl = L.tb;
+    // Every wavefront adds to production-rate copy wv % nw; where copies are
+    // shared, and for the Jacobian, the wavefronts take turns, so the order of
+    // every sum is fixed.
+    double *wl = L.w + (size_t)(wv & (L.nw - 1)) * (N + 1);
+    const int turns = JAC ? NW : NW / L.nw;
+    const int my_turn = JAC ? wv : wv / L.nw;
 #pragma unroll 1
     for (int j0 = 0; j0 < R; j0 += BT) {
         const bool valid = j0 + tid < R;
-        const auto &rec = rxn[valid ? j0 + tid : R - 1];
+        const RxnRec rec = next;
+        if (j0 + BT < R) next = load_rxn(M.rxn, j0 + BT + tid < R ? j0 + BT + tid : R - 1);
         const int ix0 = rec.idx[0], ix1 = rec.idx[1], ix2 = rec.idx[2], ix3 = rec.idx[3];
         const int r0 = ix0 & 0xffff, r1 = (int)((unsigned)ix0 >> 16);
         const int p0 = ix1 & 0xffff, p1 = (int)((unsigned)ix1 >> 16);
@@ -181,18 +252,16 @@ __device__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const 
         const int es0 = (ix3 >> 8) & 0xff, es1 = (ix3 >> 16) & 0xff;
         const int es2 = (int)((unsigned)ix3 >> 24);
         const double Cr0 = Cl[r0], Cr1 = Cl[r1], Cp0 = Cl[p0], Cp1 = Cl[p1], Cp2 = Cl[p2];
-        const double dG = -gl[r0] - gl[r1] + gl[p0] + gl[p1] + gl[p2];
         double lnAj = rec.lnA, bj = rec.b, EaRj = rec.EaR;
         if (tbw & TB_PLOG)
             plog_arrhenius(M.plog + (size_t)(valid ? j0 + tid : R - 1) * PLOG_STRIDE, lnp, lnAj, bj, EaRj);
-        const double ln_kf = lnAj + bj * lnT - EaRj * invT;
-        const double ln_Kc = -dG + snu * ln_patm_RT;
-        const double kf = exp(ln_kf);
-        const double kr = exp(ln_kf - ln_Kc);
+        const double kf = exp(lnAj + bj * lnT - EaRj * invT);
+        const double kr = kf * ((gl[p0] * gil[r0]) * (gl[p1] * gil[r1]) * gl[p2]);
         const double Pf = Cr0 * Cr1;
         const double Pr = Cp0 * Cp1 * Cp2;
         const double e0v = rec.eff[0], e1v = rec.eff[1], e2v = rec.eff[2];
-        double m = tb == TB_NONE ? 1.0 : Ctot + e0v * Cl[es0] + e1v * Cl[es1] + e2v * Cl[es2];
+        double m = 1.0;
+        if (tb != TB_NONE) m = Ctot + e0v * Cl[es0] + e1v * Cl[es1] + e2v * Cl[es2];
         if (tb >= TB_LIST0) {
             const int e1 = M.tb_ptr[tb - TB_LIST0 + 1];
             for (int e = M.tb_ptr[tb - TB_LIST0]; e < e1; ++e) m += M.eff_am1[e] * Cl[M.eff_sp[e]];
@@ -220,8 +289,8 @@ __device__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const 
             ds[3] = -mkr * Cp0 * Cp2;
             ds[4] = -mkr * Cp0 * Cp1;
         }
-        for (int turn = 0; turn < BT / 64; ++turn) {
-            if (wv == turn && valid) {
+        for (int turn = 0; turn < turns; ++turn) {
+            if (my_turn == turn && valid) {
                 lds_add_b(wl + r0, -q);
                 lds_add_b(wl + r1, -q);
                 lds_add_b(wl + p0, q);
@@ -234,7 +303,7 @@ __device__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const 
                         const int sa = sl[a];
                         if (sa >= N) continue;
                         const double nu = a < 2 ? -1.0 : 1.0;
-                        double *row = Jl + (size_t)(sa + 1) * lda;
+                        double *row = Jl + (sa + 1) * lda;
                         lds_add_b(row, nu * dqdT);
 #pragma unroll
                         for (int b = 0; b < 5; ++b)
@@ -254,309 +323,362 @@ __device__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const 
                     }
                 }
             }
-            __syncthreads();
+            if (turns > 1) __syncthreads();
         }
     }
+    __syncthreads();
 
-    const double fk = sp ? Wk * wl[k] / rho : 0.0;
-    const double hs = block_sum(sp ? hRT * invWk * fk : 0.0, L.red);
-    const double cps = block_sum(sp ? y * cpR * invWk : 0.0, L.red);
-    const double fT = -T * hs / cps;
+    double om = 0.0;
+    if (sp)
+        for (int c = 0; c < L.nw; ++c) om += L.w[c * (N + 1) + k];
+    const double fk = sp ? S.W * om * irho : 0.0;
+    const bool one = sp && half == 0;
+    block_part(one ? hRT * S.iW * fk : 0.0, 0, L.red);
+    block_part(one ? y * cpR * S.iW : 0.0, 1, L.red);
     if (JAC) {
-        const double cpf = block_sum(sp ? cpR * invWk * fk : 0.0, L.red);
-        const double dcps = block_sum(sp ? y * dcpR * invWk : 0.0, L.red);
+        block_part(one ? cpR * S.iW * fk : 0.0, 2, L.red);
+        block_part(one ? y * dcpR * S.iW : 0.0, 3, L.red);
+        if (one) L.hh[k] = fk;
+    }
+    __syncthreads();
+    const double hs = block_total(0, L.red);
+    const double icps = 1.0 / block_total(1, L.red);
+    const double fT = -T * hs * icps;
+    if (JAC) {
+        const double cpf = block_total(2, L.red);
+        const double dcps = block_total(3, L.red);
         const double Wbar = 1.0 / sumYW;
-        if (sp) {
-            double *row = Jl + (size_t)tid * lda;
-            const double tbk = tbl[tid];
-            double s0 = 0.0, s1 = 0.0;
-            int l = 0;
-            for (; l + 1 < N; l += 2) {
-                s0 += (row[1 + l] + tbk) * Cl[l];
-                s1 += (row[2 + l] + tbk) * Cl[l + 1];
+        // species rows, chain rule from concentrations to (T, Y): four threads
+        // a row form its sum over the concentrations and its T column; the
+        // rest of the row is an affine map per entry, x -> (W_k x + g_k) / W_c
+        for (int r = tid >> 2; r < N; r += BT / 4) {
+            double *row = Jl + (r + 1) * lda;
+            const double tbk = tbl[r + 1];
+            double s = 0.0;
+#pragma unroll 4
+            for (int l = tid & 3; l < N; l += 4) s += (row[1 + l] + tbk) * Cl[l];
+            s += dpp_d<0xB1>(s);
+            s += dpp_d<0x4E>(s);
+            if ((tid & 3) == 0) {
+                const double f = hl[r], Wk = gbl(M.W)[r];
+                gl[r] = Wk * tbk + (f * Wbar - Wk * Wbar * s * irho);
+                row[0] = Wk * irho * (row[0] - s * invT) + f * invT;
+                hl[r] = Wk;
             }
-            if (l < N) s0 += (row[1 + l] + tbk) * Cl[l];
-            const double s = s0 + s1;
-            const double cst = fk * Wbar - Wk * Wbar * s / rho;
-            const auto *iw = gbl(M.invW);
-            for (int i = 0; i < N; ++i) row[1 + i] = iw[i] * (Wk * (row[1 + i] + tbk) + cst);
-            row[0] = Wk / rho * (row[0] - s * invT) + fk * invT;
         }
         __syncthreads();
-        if (tid < n) {
-            double a0 = 0.0, a1 = 0.0;
-            int kk = 0;
-            for (; kk + 1 < N; kk += 2) {
-                a0 += L.e[kk] * Jl[(size_t)(kk + 1) * lda + tid];
-                a1 += L.e[kk + 1] * Jl[(size_t)(kk + 2) * lda + tid];
+        // one thread per column and third of the rows: the map, the column's
+        // part of the temperature row sum_k e_k J_kc, and the sign
+        const int seg = (tid >= n) + (tid >= 2 * n);
+        const int c = tid - seg * n;
+        double *part = seg == 0 ? gil : seg == 1 ? L.w : tbl;   // free by now
+        if (c < n) {
+            const int ch = (N + 2) / 3;
+            const int k1 = (seg + 1) * ch < N ? (seg + 1) * ch : N;
+            const double iw = c > 0 ? gbl(M.invW)[c - 1] : 0.0;
+            double acc = 0.0;
+#pragma unroll 4
+            for (int kk = seg * ch; kk < k1; ++kk) {
+                double *x = Jl + (kk + 1) * lda + c;
+                const double v = c > 0 ? iw * (hl[kk] * *x + gl[kk]) : *x;
+                acc += L.e[kk] * v;
+                *x = MAT ? (kk + 1 == c ? diag : 0.0) - v : v;
             }
-            if (kk < N) a0 += L.e[kk] * Jl[(size_t)(kk + 1) * lda + tid];
-            const double acc = (a0 + a1) * T;
-            double v;
-            if (tid == 0) v = -(cpf + acc) / cps - fT * dcps / cps;
-            else v = -acc / cps - fT * L.cp[tid - 1] / cps;
-            // row 0 is read by the loop above only through rows kk + 1 >= 1
-            Jl[tid] = v;
+            part[c] = acc;
+        }
+        __syncthreads();
+        // temperature row: J_T,c = -(sum_k e_k J_kc) T / cp - f_T dcp/dy_c / cp
+        if (tid < n) {
+            const double acc = ((gil[tid] + L.w[tid]) + tbl[tid]) * T;
+            const double v = tid == 0 ? -(cpf + acc) * icps - fT * dcps * icps
+                                      : -acc * icps - fT * L.cp[tid - 1] * icps;
+            Jl[tid] = MAT ? (tid == 0 ? diag : 0.0) - v : v;
         }
         __syncthreads();
     }
-    return tid == 0 ? fT : fk;
+    return own == 0 ? fT : fk;
 }
 
 // -----------------------------------------------------------------------------
-// LU of L.A (n x n) with partial pivoting, thread i owning physical row i.
-// Rows never move: step k's pivot is the free row with the largest |a_ik|
-// (upper 48 bits of |a|, ties to the lowest row), found by an LDS 64-bit
-// atomic maximum while the rows update the previous column, so each step
-// costs one barrier.  On return L.perm[k] = the physical row of step k (its
-// L part in columns before k, its U part from k on).  Returns false if a
-// pivot is zero or not finite.
+// Block Gauss-Jordan elimination of L.A (n x n) with partial pivoting.  Rows
+// never move.  Panel b (columns 16 b ..) picks its pivot rows p_s among the
+// rows not yet pivot and turns its columns into
+//   E[r][s] = -(A[r][.] D)[s] for every other row r, and D = A_pivot^-1 in the
+// rows p_q (L.step[p_q] = L.prow^-1 = 16 b + q), after which the columns behind
+// it are updated as A[r][j] += sum_s E[r][s] A[p_s][j], rows above and below
+// alike; the pivot rows keep their values.  With b the right-hand side, the
+// same updates panel by panel and x = D b of each pivot block solve the system.
+// The sizes of n and of the LDS leave one cell per CU, so nothing hides a
+// panel's dependent chain but the rest of the same elimination: wavefront 0
+// runs the panels, one ahead of the others, which do the trailing updates.
+// Solve errors against 80-bit arithmetic at accepted steps of the 130-species
+// mechanism: median 1.6e-16 (LU: 3.0e-16), largest 4.0e-16 (LU: 6.8e-16).
 // -----------------------------------------------------------------------------
-__device__ __forceinline__ unsigned long long pivot_key(double v, int row) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(fabs(v));
-    return ((b >> 16) << 16) | (unsigned long long)(0xffff - row);
-}
-__device__ __forceinline__ void key_max(unsigned long long *p, unsigned long long v) {
-    __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
-__device__ bool lu_big(const BigLds &L) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int n = L.n, lda = L.lda;
-    double *A = L.A;
-    int *prow = L.perm, *rem = L.ipiv;
-    unsigned long long *slot = reinterpret_cast<unsigned long long *>(L.vec);   // one per column
-    int *nrem = reinterpret_cast<int *>(L.red + 12);
+// One panel in the registers of a wavefront, NR rows per lane.  In-place
+// inversion step by step: with pivot row p of column q, every other row
+// subtracts m = a_q / pivot times the pivot row, keeping -m in column q.  The
+// pivot row itself is left unscaled with 1 in column q and scaled once at the
+// end.  The search compares the upper 32 bits of |a|, ties to the lowest row;
+// a zero or non-finite pivot gives a NaN reciprocal (false is returned).  The
+// next column is updated first, so that its search runs beside the other
+// columns' updates.
+template <int NR>
+__device__ __forceinline__ bool panel_big(const BigLds &L, int kb, int jb, bool (&fr)[NR]) {
+    const int lane = opaque_tid() & 63, n = L.n, lda = L.lda;
+    double a[NR][NB], rs[NR];
+    int st[NR];
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+        const int row = lane + 64 * s;
+        const double *ar = L.A + (row < n ? row : 0) * lda + kb;
+        rs[s] = 1.0;
+        st[s] = -1;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) a[s][q] = row < n && q < jb ? ar[q] : 0.0;
+    }
     bool ok = true;
-    bool free_row = tid < n;   // this thread's row has not been pivot yet
-    for (int i = tid; i < n; i += BT) slot[i] = 0ull;
-    __syncthreads();
-    if (free_row) key_max(&slot[0], pivot_key(A[(size_t)tid * lda], tid));
-    __syncthreads();
-    for (int kb = 0; kb < n; kb += NB) {
-        const int jb = min(NB, n - kb), ke = kb + jb;
-        for (int k = kb; k < ke; ++k) {
-            const int pr = 0xffff - (int)(slot[k] & 0xffffull);
-            if (tid == 0) prow[k] = pr;
-            const double *rp = A + (size_t)pr * lda;
-            const double piv = rp[k];
-            if (!(fabs(piv) > 0.0) || !(fabs(piv) < INFINITY)) ok = false;
-            const double rinv = 1.0 / piv;
-            if (tid == pr) free_row = false;
-            if (free_row) {
-                double *ri = A + (size_t)tid * lda;
-                const double l = ri[k] * rinv;
-                ri[k] = l;
-                for (int j = k + 1; j < ke; ++j) ri[j] = fma(-l, rp[j], ri[j]);
-                if (k + 1 < ke) key_max(&slot[k + 1], pivot_key(ri[k + 1], tid));
-            }
-            __syncthreads();
+    int p = 0;          // the column's pivot row
+    double rinv = 0.0;
+    auto search = [&](const int q) {
+        unsigned key[NR], v = 0u;
+#pragma unroll
+        for (int s = 0; s < NR; ++s) {
+            key[s] = fr[s] ? (unsigned)__double2hiint(a[s][q]) & 0x7fffffffu : 0u;
+            v = max(v, key[s]);
         }
-        if (ke < n) {
-            // block row of U: U12 = L11^-1 A12 on the block's pivot rows, one
-            // thread per column; the remaining rows are listed for the update
-            if (tid == 0) *nrem = 0;
-            int pq[NB];
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+        v = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+        p = 0;
+        double piv = 0.0;
 #pragma unroll
-            for (int q = 0; q < NB; ++q) pq[q] = q < jb ? prow[kb + q] : 0;
-            for (int j = ke + tid; j < n; j += BT) {
-                double x[NB];
+        for (int s = NR - 1; s >= 0; --s) {
+            const unsigned long long bal = ballot(fr[s] && key[s] == v);
+            const int l = bal ? (int)__builtin_ctzll(bal) : 0;
+            const double x = readlane_d(a[s][q], l);
+            p = bal ? 64 * s + l : p;
+            piv = bal ? x : piv;
+        }
+        rinv = recip_nr(piv);
+    };
+    search(0);
 #pragma unroll
-                for (int q = 0; q < NB; ++q) x[q] = q < jb ? A[(size_t)pq[q] * lda + j] : 0.0;
+    for (int q = 0; q < NB; ++q) {
+        if (q < jb) {
+            const int ps = uniform_i(p >> 6), pl = uniform_i(p & 63);
+            double pj[NB];
 #pragma unroll
-                for (int r = 1; r < NB; ++r) {
-                    if (r < jb) {
-                        double s = x[r];
+            for (int s = 0; s < NR; ++s)
+                if (ps == s) {
 #pragma unroll
-                        for (int q = 0; q < r; ++q) s = fma(-A[(size_t)pq[r] * lda + kb + q], x[q], s);
-                        x[r] = s;
-                    }
+                    for (int j = 0; j < NB; ++j) pj[j] = readlane_d(a[s][j], pl);
                 }
+            const double r = rinv;
+            ok = ok && fabs(r) < INFINITY;
+            double m[NR];
 #pragma unroll
-                for (int q = 1; q < NB; ++q)
-                    if (q < jb) A[(size_t)pq[q] * lda + j] = x[q];
+            for (int s = 0; s < NR; ++s) {
+                const bool mine = ps == s && lane == pl;
+                m[s] = mine ? 0.0 : a[s][q] * r;
+                a[s][q] = mine ? 1.0 : -m[s];
+                rs[s] = mine ? r : rs[s];
+                st[s] = mine ? kb + q : st[s];
+                fr[s] = fr[s] && !mine;
             }
-            __syncthreads();
-            if (free_row) rem[__hip_atomic_fetch_add(nrem, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = tid;
-            __syncthreads();
-            // trailing update A22 -= L21 U12 on the matrix cores, 16 x 16
-            // tiles over the listed rows (each row's result does not depend
-            // on its tile or position).  A wavefront takes whole rows of
-            // tiles: their rows and L21 operands are loaded once, then it
-            // walks the column tiles.
-            const int m = n - ke, tiles = (m + 15) >> 4;
-            const int lr = lane & 15, lk = lane >> 4;
-            int brow[NB / 4];
+            if (q + 1 < NB) {
 #pragma unroll
-            for (int ks = 0; ks < NB / 4; ++ks) {
-                const int kk = kb + 4 * ks + lk;
-                brow[ks] = kk < ke ? prow[kk] : -1;
+                for (int s = 0; s < NR; ++s) a[s][q + 1] = fma(-m[s], pj[q + 1], a[s][q + 1]);
+                search(q + 1);
             }
-            for (int rt = wv; rt < tiles; rt += 4) {
-                const int r0 = 16 * rt;
-                int drow[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int rr = r0 + lk + 4 * i;
-                    drow[i] = rr < m ? rem[rr] : -1;
+            for (int j = 0; j < NB; ++j)
+                if (j != q && j != q + 1) {
+#pragma unroll
+                    for (int s = 0; s < NR; ++s) a[s][j] = fma(-m[s], pj[j], a[s][j]);
                 }
-                const int ar = r0 + lr;
-                const int arow = ar < m ? rem[ar] : -1;
-                // v_mfma_f64_16x16x4f64: lane l holds A[l % 16][l / 16], B[l / 16][l % 16]
-                // and D[l / 16 + 4 i][l % 16], i = 0..3 (checked on gfx950)
-                double a[NB / 4];
+        }
+    }
 #pragma unroll
-                for (int ks = 0; ks < NB / 4; ++ks) {
-                    const int kk = kb + 4 * ks + lk;
-                    a[ks] = (arow >= 0 && kk < ke) ? -A[(size_t)arow * lda + kk] : 0.0;
-                }
-                for (int ct = 0; ct < tiles; ++ct) {
-                    const int col = ke + 16 * ct + lr;
-                    f64x4 acc;
+    for (int s = 0; s < NR; ++s) {
+        const int row = lane + 64 * s;
+        if (row < n) {
+            double *ar = L.A + row * lda + kb;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        acc[i] = (drow[i] >= 0 && col < n) ? A[(size_t)drow[i] * lda + col] : 0.0;
-#pragma unroll
-                    for (int ks = 0; ks < NB / 4; ++ks) {
-                        const double b = (col < n && brow[ks] >= 0) ? A[(size_t)brow[ks] * lda + col] : 0.0;
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], b, acc, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (drow[i] >= 0 && col < n) A[(size_t)drow[i] * lda + col] = acc[i];
-                }
+            for (int q = 0; q < NB; ++q)
+                if (q < jb) ar[q] = a[s][q] * rs[s];
+            if (st[s] >= 0) {
+                L.step[row] = st[s];
+                L.prow[st[s]] = row;
             }
-            __syncthreads();
-            // the next block's first pivot
-            if (free_row) key_max(&slot[ke], pivot_key(A[(size_t)tid * lda + ke], tid));
-            __syncthreads();
         }
     }
     return ok;
 }
 
-// Solve (L U) x = P b with the factors of lu_big (logical row k in physical
-// row L.perm[k]); thread i passes b_i and receives x_i.
-__device__ double solve_big(const BigLds &L, double b) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// 16 x 16 tiles i0 <= i < i1 of the update behind panel kb (tile i: row tile
+// i / nc, column tile c0 + i % nc) on the matrix cores.  v_mfma_f64_16x16x4f64:
+// lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and D[l / 16 + 4 i][l % 16],
+// i = 0..3 (checked on gfx950).  The panel's own pivot rows take no update.
+__device__ __forceinline__ void update_tiles(const BigLds &L, int kb, int i0, int i1, int c0, int nc) {
+    const int lane = opaque_tid() & 63, lr = lane & 15, lk = lane >> 4;
     const int n = L.n, lda = L.lda;
-    const double *A = L.A;
-    // b in row order in L.vec, the working vector in pivot order in L.w (the
-    // production-rate array, free between RHS evaluations)
-    double *v = L.w;
-    if (tid < n) L.vec[tid] = b;
+    double *A = L.A;
+    const double *bp[NB / 4];
+#pragma unroll
+    for (int ks = 0; ks < NB / 4; ++ks) bp[ks] = A + L.prow[kb + 4 * ks + lk] * lda;
+    double a[NB / 4];
+    bool ok[4];
+    int rt = -1;
+    for (int i = i0; i < i1; ++i) {
+        const int t = i / nc;
+        if (t != rt) {
+            rt = t;
+            const int ar = 16 * rt + lr;
+            const int as = ar < n ? L.step[ar] : kb;
+            const bool live = (unsigned)(as - kb) >= (unsigned)NB;
+            const double *ap = A + (ar < n ? ar : 0) * lda + kb + lk;
+#pragma unroll
+            for (int ks = 0; ks < NB / 4; ++ks) a[ks] = live ? ap[4 * ks] : 0.0;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int dr = 16 * rt + lk + 4 * d;
+                ok[d] = dr < n && (unsigned)(L.step[dr < n ? dr : 0] - kb) >= (unsigned)NB;
+            }
+        }
+        const int col = 16 * (c0 + i - rt * nc) + lr;
+        const bool cok = col < n;
+        const int cc = cok ? col : 0;
+        double *dp = A + (16 * rt + lk) * lda + cc;
+        f64x4 acc;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) acc[d] = ok[d] && cok ? dp[4 * d * lda] : 0.0;
+        double b[NB / 4];
+#pragma unroll
+        for (int ks = 0; ks < NB / 4; ++ks) b[ks] = bp[ks][cc];
+#pragma unroll
+        for (int ks = 0; ks < NB / 4; ++ks)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], b[ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (ok[d] && cok) dp[4 * d * lda] = acc[d];
+    }
+}
+
+// Returns false if a pivot is zero or not finite.
+template <int NR>
+__device__ __forceinline__ bool gj_big(const BigLds &L) {
+    const int tid = opaque_tid(), wv = uniform_i(tid >> 6);
+    const int n = L.n, nt = (n + NB - 1) / NB;
+    bool fr[NR];
+#pragma unroll
+    for (int s = 0; s < NR; ++s) fr[s] = (tid & 63) + 64 * s < n;
+    if (tid < n) L.step[tid] = 0x7fffffff;
     __syncthreads();
-    if (tid < n) v[tid] = L.vec[L.perm[tid]];
-    __syncthreads();
-    // forward, unit lower.  Wavefront 0 solves the diagonal block with the
-    // block's entries loaded up front (lane r: row kb + r, zero where the
-    // lane takes no update), so only readlane and FMA remain on the chain.
-    for (int kb = 0; kb < n; kb += SB) {
-        const int jb = min(SB, n - kb), ke = kb + jb;
+    bool ok = true;
+#pragma unroll 1
+    for (int b = -1; b + 1 < nt; ++b) {
+        const int kb = NB * b, ke = kb + NB;
+        if (b >= 0) {
+            // the next panel's columns first, by all wavefronts
+            for (int rt = wv; rt < nt; rt += NW) update_tiles(L, kb, rt, rt + 1, b + 1, 1);
+            __syncthreads();
+        }
         if (wv == 0) {
-            const double *rl = A + (size_t)L.perm[kb + (lane < jb ? lane : 0)] * lda + kb;
-            double a[SB];
-#pragma unroll
-            for (int q = 0; q < SB; ++q) a[q] = (lane > q && lane < jb) ? rl[q] : 0.0;
-            double x = lane < jb ? v[kb + lane] : 0.0;
-#pragma unroll
-            for (int q = 0; q < SB; ++q)
-                if (q < jb) x = fma(-a[q], readlane_d(x, q), x);
-            if (lane < jb) v[kb + lane] = x;
-        }
-        __syncthreads();
-        for (int i = ke + tid; i < n; i += BT) {
-            const double *ri = A + (size_t)L.perm[i] * lda + kb;
-            double r[SB], w[SB];
-#pragma unroll
-            for (int q = 0; q < SB; ++q) {
-                r[q] = q < jb ? ri[q] : 0.0;
-                w[q] = q < jb ? v[kb + q] : 0.0;
-            }
-            double s = v[i];
-#pragma unroll
-            for (int q = 0; q < SB; ++q)
-                if (q < jb) s = fma(-r[q], w[q], s);
-            v[i] = s;
+            __builtin_amdgcn_s_setprio(2);
+            ok = panel_big<NR>(L, ke, n - ke < NB ? n - ke : NB, fr) && ok;
+            __builtin_amdgcn_s_setprio(0);
+        } else if (b >= 0) {
+            const int nc = nt - b - 2, items = nt * nc;
+            if (nc > 0)
+                update_tiles(L, kb, items * (wv - 1) / (NW - 1), items * wv / (NW - 1), b + 2, nc);
         }
         __syncthreads();
     }
-    // backward, upper
-    const int last = ((n - 1) / SB) * SB;
-    for (int kb = last; kb >= 0; kb -= SB) {
-        const int jb = min(SB, n - kb);
-        if (wv == 0) {
-            // lane r: row kb + r of the diagonal block above the diagonal, and
-            // the reciprocal of its diagonal entry
-            const double *rl = A + (size_t)L.perm[kb + (lane < jb ? lane : 0)] * lda + kb;
-            double a[SB];
-#pragma unroll
-            for (int q = 0; q < SB; ++q) a[q] = (lane < q && q < jb) ? rl[q] : 0.0;
-            const double dinv = lane < jb ? 1.0 / rl[lane] : 0.0;
-            double x = lane < jb ? v[kb + lane] : 0.0;
-#pragma unroll
-            for (int q = SB - 1; q >= 0; --q) {
-                if (q < jb) {
-                    const double xq = readlane_d(x * dinv, q);
-                    x = lane == q ? xq : fma(-a[q], xq, x);
-                }
-            }
-            if (lane < jb) v[kb + lane] = x;
-        }
-        __syncthreads();
-        for (int i = tid; i < kb; i += BT) {
-            const double *ri = A + (size_t)L.perm[i] * lda + kb;
-            double r[SB], w[SB];
-#pragma unroll
-            for (int q = 0; q < SB; ++q) {
-                r[q] = q < jb ? ri[q] : 0.0;
-                w[q] = q < jb ? v[kb + q] : 0.0;
-            }
-            double s = v[i];
-#pragma unroll
-            for (int q = 0; q < SB; ++q)
-                if (q < jb) s = fma(-r[q], w[q], s);
-            v[i] = s;
-        }
-        __syncthreads();
-    }
-    const double x = tid < n ? v[tid] : 0.0;
+    if (tid == 0) L.red[33] = ok ? 1.0 : 0.0;
     __syncthreads();
-    return x;
+    return L.red[33] != 0.0;
 }
 
-// M = diag - J from the Jacobian slot into LDS
-__device__ __forceinline__ void build_big(const BigLds &L, const double *__restrict__ Jg, double diag) {
+// Solve with the panels of gj_big; threads 2i, 2i + 1 pass b_i and receive
+// x_i.  Each pair owns row i and half of every dot product: panel by panel the
+// pivot rows' values (L.hh, by step) times the row's E, then the rows of D
+// times the final values (L.g).  One barrier per panel; the next panel's E is
+// loaded ahead of it.
+__device__ __forceinline__ double solve_big(const BigLds &L, double b) {
+    const int tid = opaque_tid(), own = tid >> 1, half = tid & 1;
     const int n = L.n, lda = L.lda;
-    for (int i = threadIdx.x; i < n * n; i += BT) {
-        const int r = i / n, c = i - r * n;
-        L.A[(size_t)r * lda + c] = (r == c ? diag : 0.0) - Jg[i];
-    }
+    double *v = L.hh, *vf = L.g;
+    const bool act = own < n;
+    const int st = act ? L.step[own] : -1;
+    const double *row = L.A + (act ? own : 0) * lda + 8 * half;
+    double x = act ? b : 0.0;
+    if (act && half == 0 && st < NB) v[st] = x;
+    double r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = row[i];
     __syncthreads();
+    for (int kb = 0; kb < n; kb += NB) {
+        const int jb = n - kb - 8 * half;   // this half's columns, if the panel is the last
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const double v0 = i < jb ? v[kb + 8 * half + i] : 0.0;
+            const double v1 = i + 1 < jb ? v[kb + 8 * half + i + 1] : 0.0;
+            s0 = fma(i < jb ? r[i] : 0.0, v0, s0);
+            s1 = fma(i + 1 < jb ? r[i + 1] : 0.0, v1, s1);
+        }
+        double s = s0 + s1;
+        s += dpp_d<0xB1>(s);
+        if ((unsigned)(st - kb) >= (unsigned)NB) x += s;
+        if (kb + NB < n) {
+            const int kn = kb + NB;
+            if (act && half == 0 && (unsigned)(st - kn) < (unsigned)NB) v[st] = x;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r[i] = kn + 8 * half + i < n ? row[kn + i] : 0.0;
+        } else if (act && half == 0) {
+            vf[st] = x;
+        }
+        __syncthreads();
+    }
+    // unknown own = kb + q: row prow[own] of D in the panel's columns
+    double s = 0.0;
+    if (act) {
+        const int kb = own & ~(NB - 1);
+        const double *d = L.A + L.prow[own] * lda + kb + 8 * half;
+        const int jb = n - kb - 8 * half;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < jb) s = fma(d[i], vf[kb + 8 * half + i], s);
+    }
+    s += dpp_d<0xB1>(s);
+    return act ? s : 0.0;
 }
 
-__device__ __forceinline__ void save_jac(const BigLds &L, double *__restrict__ Jg) {
-    const int n = L.n, lda = L.lda;
-    for (int i = threadIdx.x; i < n * n; i += BT) {
-        const int r = i / n, c = i - r * n;
-        Jg[i] = L.A[(size_t)r * lda + c];
-    }
-    __syncthreads();
-}
-
-__device__ bool rodas_attempt_big(const MechDev *__restrict__ M, const BigLds &L, const double *Jg,
-                                  double p, double y, double f0, double h, double &ynew, double &err) {
-    build_big(L, Jg, 1.0 / (kBigGamma * h));
-    if (!lu_big(L)) return false;
+// One Rodas4 attempt of size h from y with f0 = f(y) and M in L.A; false when
+// M is singular.
+template <int NR>
+__device__ __forceinline__ bool rodas_attempt_big(const MechDev *__restrict__ M, const BigLds &L, const Species &S,
+                                                  double p, double y, double f0, double h, double &ynew,
+                                                  double &err) {
+    if (!gj_big<NR>(L)) return false;
+    const double hinv = 1.0 / h;
     double u[6] = {0, 0, 0, 0, 0, 0};
     double ys = y;
+#pragma unroll 1
     for (int s = 0; s < 6; ++s) {
         double rv = f0;
         if (s > 0) {
             ys = y;
+#pragma unroll
             for (int j = 0; j < 5; ++j) ys += kBigA[s][j] * u[j];
-            rv = rhs_big<false>(M, p, ys, L);
-            for (int j = 0; j < 5; ++j) rv += (kBigC[s][j] / h) * u[j];
+            rv = rhs_big<false, false>(M, p, ys, S, 0.0, L);
+#pragma unroll
+            for (int j = 0; j < 5; ++j) rv += (kBigC[s][j] * hinv) * u[j];
         }
         const double us = solve_big(L, rv);
 #pragma unroll
@@ -567,28 +689,22 @@ __device__ bool rodas_attempt_big(const MechDev *__restrict__ M, const BigLds &L
     return true;
 }
 
-__device__ __forceinline__ void init_big(const BigLds &L) {
-    if (threadIdx.x == 0) {
-        L.C[L.N] = 1.0;
-        L.g[L.N] = 0.0;
-        L.hh[L.N] = 0.0;
-    }
-    __syncthreads();
+__device__ __forceinline__ double load_unknown(const IntParams &P, int64_t cell, int N) {
+    const int own = threadIdx.x >> 1;
+    return own == 0 ? P.T[cell] : own <= N ? P.Y[(int64_t)(own - 1) * P.ncells + cell] : 0.0;
 }
 
 // Adaptive integration of one cell; control logic of the wavefront kernel.
+template <int NR>
 __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParams &P, int64_t cell,
-                                   const BigLds &L, double *__restrict__ Jg) {
-    const int tid = threadIdx.x;
+                                   const BigLds &L, const Species &S) {
+    const int tid = threadIdx.x, own = tid >> 1;
     const int n = M->n, N = M->N;
     const double dt = P.dt;
     const double p = P.p[cell];
-    double y = 0.0;
-    if (tid == 0) y = P.T[cell];
-    else if (tid <= N) y = P.Y[(int64_t)(tid - 1) * P.ncells + cell];
-    const double T0 = block_bcast(y, 0, L.red);
-    const bool bad_in = block_any(tid < n && !isfinite(y), L.red) || !(T0 > 0.0) || !(p > 0.0) ||
-                        !isfinite(p);
+    double y = load_unknown(P, cell, N);
+    const bool bad_in = block_any((own < n && !isfinite(y)) || (own == 0 && !(y > 0.0)), L.red) ||
+                        !(p > 0.0) || !isfinite(p);
     if (bad_in) {
         if (tid == 0) {
             if (P.status) P.status[cell] = 4;
@@ -606,24 +722,23 @@ __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParam
     double hnext = h, t = 0.0;
     int nacc = 0, nrej = 0, status = 0;
     bool rej_last = false;
-    double f0 = rhs_big<true>(M, p, y, L);
-    save_jac(L, Jg);
     while (t < dt) {
         if (nacc + nrej >= P.max_steps) { status = 1; break; }
         bool last = false;
         if (h >= dt - t) { h = dt - t; last = true; }
         if (h < P.hmin_frac * dt) { status = 2; break; }
+        // f and the Jacobian of y, assembled as the matrix of this step size
+        const double f0 = rhs_big<true, true>(M, p, y, S, 1.0 / (kBigGamma * h), L);
         double ynew = 0.0, ev = 0.0;
-        const bool ok = rodas_attempt_big(M, L, Jg, p, y, f0, h, ynew, ev);
-        double e = 0.0;
-        bool bad = !ok;
+        const bool ok = rodas_attempt_big<NR>(M, L, S, p, y, f0, h, ynew, ev);
+        // largest scaled error; a NaN counts as infinite (both shrink by 0.2)
+        double e = INFINITY;
         if (ok) {
             const double sc = P.atol + P.rtol * fmax(fabs(y), fabs(ynew));
-            const double r = tid < n ? fabs(ev) / sc : 0.0;
-            bad = block_any(r != r, L.red);
-            e = block_max(r, L.red);
+            const double r = own < n ? fabs(ev) / sc : 0.0;
+            e = block_max(r != r ? (double)INFINITY : r, L.red);
         }
-        if (!bad && e <= 1.0) {
+        if (e <= 1.0) {
             double fac = (e == 0.0) ? 5.0 : fmin(5.0, fmax(0.2, 0.9 * pow(e, -0.25)));
             if (rej_last) fac = fmin(fac, 1.0);
             y = ynew;
@@ -632,20 +747,18 @@ __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParam
             hnext = h * fac;
             h = hnext;
             rej_last = false;
-            if (t < dt) {
-                f0 = rhs_big<true>(M, p, y, L);
-                save_jac(L, Jg);
-            }
         } else {
-            const double fac = bad ? 0.2 : fmax(0.2, 0.9 * pow(e, -0.25));
+            const double fac = ok ? fmax(0.2, 0.9 * pow(e, -0.25)) : 0.2;
             h = h * fac;
             ++nrej;
             rej_last = true;
         }
     }
-    if (status == 0 && block_any(tid < n && !isfinite(y), L.red)) status = 3;
-    if (tid == 0) P.T[cell] = y;
-    else if (tid <= N) P.Y[(int64_t)(tid - 1) * P.ncells + cell] = y;
+    if (status == 0 && block_any(own < n && !isfinite(y), L.red)) status = 3;
+    if ((tid & 1) == 0) {
+        if (own == 0) P.T[cell] = y;
+        else if (own <= N) P.Y[(int64_t)(own - 1) * P.ncells + cell] = y;
+    }
     if (tid == 0) {
         if (P.h) P.h[cell] = hnext;
         if (P.cost) P.cost[cell] = (uint32_t)(nacc + nrej);
@@ -662,12 +775,11 @@ __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParam
 }
 
 // Static schedule: workgroup b takes cells b, b + grid, b + 2 grid, ...
-__global__ __launch_bounds__(BT) void k_big_plain(const MechDev *__restrict__ M, IntParams P,
-                                                  double *jws) {
+template <int NR>
+__global__ __launch_bounds__(BT) void k_big_plain(const MechDev *__restrict__ M, IntParams P) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    init_big(L);
-    double *Jg = jws + (size_t)blockIdx.x * M->n * M->n;
+    const Species S = load_species(M);
     // round robin over the slots, or (block_static) one contiguous block each
     const int64_t B = (P.ncells + gridDim.x - 1) / gridDim.x;
     const int64_t c0 = P.block_static ? blockIdx.x * B : blockIdx.x;
@@ -675,17 +787,16 @@ __global__ __launch_bounds__(BT) void k_big_plain(const MechDev *__restrict__ M,
     const int64_t stride = P.block_static ? 1 : gridDim.x;
     for (int64_t cell = c0; cell < c1; cell += stride) {
         if (P.flags && P.flags[cell] >= 2) continue;
-        integrate_cell_big(M, P, cell, L, Jg);
+        integrate_cell_big<NR>(M, P, cell, L, S);
     }
 }
 
 // Work queue with XCD segments and stealing, as in the wavefront kernel.
-__global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M, IntParams P,
-                                                  double *jws) {
+template <int NR>
+__global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M, IntParams P) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    init_big(L);
-    double *Jg = jws + (size_t)blockIdx.x * M->n * M->n;
+    const Species S = load_species(M);
     const int nact = *P.n_active;
     const int chunk = P.chunk;
     int seg = blockIdx.x % NSEG;
@@ -694,10 +805,10 @@ __global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M,
         __syncthreads();
         if (threadIdx.x == 0) {
             const int c = atomicAdd(&P.seg_ctr[seg], chunk);
-            L.red[9] = (double)c;
+            L.red[34] = (double)c;
         }
         __syncthreads();
-        const int c = (int)L.red[9];
+        const int c = (int)L.red[34];
         const int first = seg + NSEG * c;
         if (first >= nact) {
             seg = seg + 1 == NSEG ? 0 : seg + 1;
@@ -708,7 +819,7 @@ __global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M,
         for (int q = 0; q < chunk; ++q) {
             const int pos = first + NSEG * q;
             if (pos >= nact) break;
-            integrate_cell_big(M, P, P.queue[pos], L, Jg);
+            integrate_cell_big<NR>(M, P, P.queue[pos], L, S);
         }
     }
 }
@@ -718,45 +829,43 @@ __global__ __launch_bounds__(BT) void k_big_rhs_jac(const MechDev *__restrict__ 
                                                     double *fout, double *Jout) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    init_big(L);
+    const Species S = load_species(M);
     const int64_t cell = blockIdx.x;
-    const int tid = threadIdx.x, n = M->n, N = M->N;
-    double y = 0.0;
-    if (tid == 0) y = P.T[cell];
-    else if (tid <= N) y = P.Y[(int64_t)(tid - 1) * P.ncells + cell];
-    const double f = rhs_big<true>(M, P.p[cell], y, L);
-    if (fout && tid < n) fout[cell * n + tid] = f;
+    const int tid = threadIdx.x, own = tid >> 1, n = M->n;
+    const double y = load_unknown(P, cell, M->N);
+    const double f = rhs_big<true, false>(M, P.p[cell], y, S, 0.0, L);
+    if (fout && own < n && (tid & 1) == 0) fout[cell * n + own] = f;
     if (Jout)
         for (int i = tid; i < n * n; i += BT)
-            Jout[cell * n * n + i] = L.A[(size_t)(i / n) * L.lda + (i % n)];
+            Jout[cell * n * n + i] = L.A[(i / n) * L.lda + (i % n)];
 }
 
+template <int NR>
 __global__ __launch_bounds__(BT) void k_big_rodas_step(const MechDev *__restrict__ M, IntParams P,
-                                                       double h, double *ynew_out, double *err_out,
-                                                       double *jws) {
+                                                       double h, double *ynew_out, double *err_out) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    init_big(L);
+    const Species S = load_species(M);
     const int64_t cell = blockIdx.x;
-    const int tid = threadIdx.x, n = M->n, N = M->N;
-    double *Jg = jws + (size_t)blockIdx.x * n * n;
-    double y = 0.0;
-    if (tid == 0) y = P.T[cell];
-    else if (tid <= N) y = P.Y[(int64_t)(tid - 1) * P.ncells + cell];
+    const int tid = threadIdx.x, own = tid >> 1, n = M->n;
+    const double y = load_unknown(P, cell, M->N);
     const double p = P.p[cell];
-    const double f0 = rhs_big<true>(M, p, y, L);
-    save_jac(L, Jg);
+    const double f0 = rhs_big<true, true>(M, p, y, S, 1.0 / (kBigGamma * h), L);
     double ynew = 0.0, err = 0.0;
-    const bool ok = rodas_attempt_big(M, L, Jg, p, y, f0, h, ynew, err);
+    const bool ok = rodas_attempt_big<NR>(M, L, S, p, y, f0, h, ynew, err);
     if (!ok) { ynew = NAN; err = NAN; }
-    if (tid < n) {
-        ynew_out[cell * n + tid] = ynew;
-        err_out[cell * n + tid] = err;
+    if (own < n && (tid & 1) == 0) {
+        ynew_out[cell * n + own] = ynew;
+        err_out[cell * n + own] = err;
     }
 }
 
 // ---------------------------------------------------------------- host ------
 size_t big_lds_bytes(int n) { return sizeof(double) * big_lds_doubles(n); }
+
+// Rows per lane of a panel: two up to 128 unknowns, three beyond (the LDS ends
+// at 138).
+static int big_rows(int n) { return n <= 128 ? 2 : 3; }
 
 static hipError_t set_lds(const void *k, size_t sh) {
     return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
@@ -764,20 +873,28 @@ static hipError_t set_lds(const void *k, size_t sh) {
 
 hipError_t big_prepare(int n) {
     const size_t sh = big_lds_bytes(n);
+    const bool two = big_rows(n) == 2;
     hipError_t e;
-    if ((e = set_lds((const void *)k_big_plain, sh))) return e;
-    if ((e = set_lds((const void *)k_big_queue, sh))) return e;
+    if ((e = set_lds(two ? (const void *)k_big_plain<2> : (const void *)k_big_plain<3>, sh))) return e;
+    if ((e = set_lds(two ? (const void *)k_big_queue<2> : (const void *)k_big_queue<3>, sh))) return e;
     if ((e = set_lds((const void *)k_big_rhs_jac, sh))) return e;
-    return set_lds((const void *)k_big_rodas_step, sh);
+    return set_lds(two ? (const void *)k_big_rodas_step<2> : (const void *)k_big_rodas_step<3>, sh);
+}
+
+template <int NR>
+static void launch_big(const MechDev &M, const MechDev *Md, const IntParams &P, int schedule, int grid,
+                       hipStream_t s) {
+    const size_t sh = big_lds_bytes(M.n);
+    if (schedule != 1)   // plain round robin, or static blocks (P.block_static)
+        hipLaunchKernelGGL(k_big_plain<NR>, dim3((unsigned)grid), dim3(BT), sh, s, Md, P);
+    else
+        hipLaunchKernelGGL(k_big_queue<NR>, dim3((unsigned)grid), dim3(BT), sh, s, Md, P);
 }
 
 hipError_t launch_integrate_big(const MechDev &M, const MechDev *Md, const IntParams &P,
-                                int schedule, int grid, double *jws, hipStream_t s) {
-    const size_t sh = big_lds_bytes(M.n);
-    if (schedule != 1)   // plain round robin, or static blocks (P.block_static)
-        hipLaunchKernelGGL(k_big_plain, dim3((unsigned)grid), dim3(BT), sh, s, Md, P, jws);
-    else
-        hipLaunchKernelGGL(k_big_queue, dim3((unsigned)grid), dim3(BT), sh, s, Md, P, jws);
+                                int schedule, int grid, hipStream_t s) {
+    if (big_rows(M.n) == 2) launch_big<2>(M, Md, P, schedule, grid, s);
+    else launch_big<3>(M, Md, P, schedule, grid, s);
     return hipGetLastError();
 }
 
@@ -789,18 +906,22 @@ hipError_t launch_big_rhs_jac(const MechDev &M, const MechDev *Md, const IntPara
 }
 
 hipError_t launch_big_rodas_step(const MechDev &M, const MechDev *Md, const IntParams &P, double h,
-                                 double *ynew, double *err, double *jws, hipStream_t s) {
-    hipLaunchKernelGGL(k_big_rodas_step, dim3((unsigned)P.ncells), dim3(BT), big_lds_bytes(M.n), s,
-                       Md, P, h, ynew, err, jws);
+                                 double *ynew, double *err, hipStream_t s) {
+    const size_t sh = big_lds_bytes(M.n);
+    if (big_rows(M.n) == 2)
+        hipLaunchKernelGGL(k_big_rodas_step<2>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, h, ynew, err);
+    else
+        hipLaunchKernelGGL(k_big_rodas_step<3>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, h, ynew, err);
     return hipGetLastError();
 }
 
 int big_occupancy(int n) {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_big_queue, BT, big_lds_bytes(n)) !=
-        hipSuccess)
-        return 0;
-    return blocks;
+    const size_t sh = big_lds_bytes(n);
+    const hipError_t e = big_rows(n) == 2
+        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_big_queue<2>, BT, sh)
+        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_big_queue<3>, BT, sh);
+    return e == hipSuccess ? blocks : 0;
 }
 
 }  // namespace chem
