@@ -138,15 +138,12 @@ __device__ __forceinline__ double block_total(int i, const double *red) {
     return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
 }
 
-// NASA-7 coefficients and molar mass of the thread's species, kept in
-// registers for the whole launch.
+// NASA-7 coefficients and molar mass of a species
 struct Species {
     double a1, a2, a3, a4, a5, a6, a7, h2, h3, h4, h5, s3, s4, s5, W, iW;
 };
-__device__ __forceinline__ Species load_species(const MechDev *__restrict__ M) {
-    const int own = threadIdx.x >> 1;
-    const int k = own >= 1 && own <= M->N ? own - 1 : 0;
-    const auto *a = gbl(M->spc) + k * SPC_STRIDE;
+__device__ __forceinline__ Species load_species(const MechDev &M, int k) {
+    const auto *a = gbl(M.spc) + k * SPC_STRIDE;
     return {a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13], a[14], a[15]};
 }
 
@@ -168,7 +165,7 @@ __device__ __forceinline__ RxnRec load_rxn(const RxnRec *__restrict__ rxn, int j
 // -----------------------------------------------------------------------------
 template <bool JAC, bool MAT>
 __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const double y,
-                                          const Species &S, const double diag, const BigLds &L) {
+                                          const double diag, const BigLds &L) {
     // The opaque thread index and sizes keep the addresses and trip counts
     // derived from them local to this call instead of held (spilled) across
     // the step loop; so below.
@@ -180,7 +177,9 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     const int lda = big_lda(n);
     const bool sp = own >= 1 && own <= N;
     const int k = sp ? own - 1 : 0;
-    // the first reaction record is on its way while the thermo runs
+    // the species record and the first reaction record are on their way while
+    // the first sums run
+    const Species S = load_species(M, k);
     RxnRec next = load_rxn(M.rxn, tid < R ? tid : R - 1);
 
     const double yw = sp ? y * S.iW : 0.0;
@@ -191,9 +190,10 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     const double sumYW = block_total(0, L.red);
     const double lnT = log(T);
     const double ln_patm_RT = kLnPatmRu - lnT;
-    const double invT = 1.0 / T;
-    const double irho = (RU_ERG * T * sumYW) / p;
-    const double rho = p / (RU_ERG * T * sumYW);
+    const double invT = recip_nr(T);
+    const double pv = RU_ERG * T * sumYW;
+    const double irho = pv * recip_nr(p);
+    const double rho = p * recip_nr(pv);
     const double Ctot = rho * sumYW;
     double cpR = 0.0, hRT = 0.0, dcpR = 0.0;
     if (sp) {
@@ -329,8 +329,18 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     __syncthreads();
 
     double om = 0.0;
-    if (sp)
-        for (int c = 0; c < L.nw; ++c) om += L.w[c * (N + 1) + k];
+    if (sp) {
+        const double *w = L.w + k;
+        if (L.nw == NW) {   // all copies loaded before the first is added
+            double x[NW];
+#pragma unroll
+            for (int c = 0; c < NW; ++c) x[c] = w[c * (N + 1)];
+#pragma unroll
+            for (int c = 0; c < NW; ++c) om += x[c];
+        } else {
+            for (int c = 0; c < L.nw; ++c) om += w[c * (N + 1)];
+        }
+    }
     const double fk = sp ? S.W * om * irho : 0.0;
     const bool one = sp && half == 0;
     block_part(one ? hRT * S.iW * fk : 0.0, 0, L.red);
@@ -342,12 +352,12 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     }
     __syncthreads();
     const double hs = block_total(0, L.red);
-    const double icps = 1.0 / block_total(1, L.red);
+    const double icps = recip_nr(block_total(1, L.red));
     const double fT = -T * hs * icps;
     if (JAC) {
         const double cpf = block_total(2, L.red);
         const double dcps = block_total(3, L.red);
-        const double Wbar = 1.0 / sumYW;
+        const double Wbar = recip_nr(sumYW);
         // species rows, chain rule from concentrations to (T, Y): four threads
         // a row form its sum over the concentrations and its T column; the
         // rest of the row is an affine map per entry, x -> (W_k x + g_k) / W_c
@@ -377,13 +387,28 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
             const int k1 = (seg + 1) * ch < N ? (seg + 1) * ch : N;
             const double iw = c > 0 ? gbl(M.invW)[c - 1] : 0.0;
             double acc = 0.0;
-#pragma unroll 4
-            for (int kk = seg * ch; kk < k1; ++kk) {
-                double *x = Jl + (kk + 1) * lda + c;
-                const double v = c > 0 ? iw * (hl[kk] * *x + gl[kk]) : *x;
-                acc += L.e[kk] * v;
-                *x = MAT ? (kk + 1 == c ? diag : 0.0) - v : v;
-            }
+            // eight rows at a time, loaded before any is written back
+            auto rows = [&](const int k0, const int cnt) {
+                double x[8], wk[8], gk[8], ek[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i >= cnt) break;
+                    x[i] = Jl[(k0 + i + 1) * lda + c];
+                    wk[i] = hl[k0 + i];
+                    gk[i] = gl[k0 + i];
+                    ek[i] = L.e[k0 + i];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i >= cnt) break;
+                    if (c > 0) x[i] = iw * (wk[i] * x[i] + gk[i]);
+                    acc += ek[i] * x[i];
+                    Jl[(k0 + i + 1) * lda + c] = MAT ? (k0 + i + 1 == c ? diag : 0.0) - x[i] : x[i];
+                }
+            };
+            int k0 = seg * ch;
+            for (; k0 + 8 <= k1; k0 += 8) rows(k0, 8);
+            for (; k0 < k1; ++k0) rows(k0, 1);
             part[c] = acc;
         }
         __syncthreads();
@@ -438,39 +463,52 @@ __device__ __forceinline__ bool panel_big(const BigLds &L, int kb, int jb, bool 
         for (int q = 0; q < NB; ++q) a[s][q] = row < n && q < jb ? ar[q] : 0.0;
     }
     bool ok = true;
-    int p = 0;          // the column's pivot row
-    double rinv = 0.0;
-    auto search = [&](const int q) {
-        unsigned key[NR], v = 0u;
+    // The search is cut into stages that the column updates are interleaved
+    // with: a lane's best of its rows, the wavefront's maximum, the lane that
+    // holds it, its slot and value, the reciprocal.
+    unsigned key = 0u, v = 0u;
+    int bs = 0, pl = 0, ps = 0;
+    double bx = 0.0, piv = 0.0, rinv = 0.0, e = 0.0;
+    auto stage = [&](const int i, const int q) {
+        switch (i) {
+            case 0: {
+                key = fr[0] ? (unsigned)__double2hiint(a[0][q]) & 0x7fffffffu : 0u;
+                bx = a[0][q];
+                bs = 0;
 #pragma unroll
-        for (int s = 0; s < NR; ++s) {
-            key[s] = fr[s] ? (unsigned)__double2hiint(a[s][q]) & 0x7fffffffu : 0u;
-            v = max(v, key[s]);
+                for (int s = 1; s < NR; ++s) {
+                    const unsigned ks = fr[s] ? (unsigned)__double2hiint(a[s][q]) & 0x7fffffffu : 0u;
+                    const bool up = ks > key;
+                    key = up ? ks : key;
+                    bx = up ? a[s][q] : bx;
+                    bs = up ? s : bs;
+                }
+                v = max(key, (unsigned)__builtin_amdgcn_update_dpp(0, (int)key, 0xB1, 0xf, 0xf, false));
+                break;
+            }
+            case 1: v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false)); break;
+            case 2: v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false)); break;
+            case 3: v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false)); break;
+            case 4: v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false)); break;
+            case 5: v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false)); break;
+            case 6: v = (unsigned)__builtin_amdgcn_readlane((int)v, 63); break;
+            case 7: pl = (int)__builtin_ctzll(ballot(key == v)); break;
+            case 8:
+                ps = __builtin_amdgcn_readlane(bs, pl);
+                piv = readlane_d(bx, pl);
+                break;
+            case 9: rinv = __builtin_amdgcn_rcp(piv); e = fma(-piv, rinv, 1.0); break;
+            case 10: rinv = fma(rinv, e, rinv); e = fma(-piv, rinv, 1.0); break;
+            default: rinv = fma(rinv, e, rinv); break;
         }
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
-        v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
-        v = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-        p = 0;
-        double piv = 0.0;
-#pragma unroll
-        for (int s = NR - 1; s >= 0; --s) {
-            const unsigned long long bal = ballot(fr[s] && key[s] == v);
-            const int l = bal ? (int)__builtin_ctzll(bal) : 0;
-            const double x = readlane_d(a[s][q], l);
-            p = bal ? 64 * s + l : p;
-            piv = bal ? x : piv;
-        }
-        rinv = recip_nr(piv);
     };
-    search(0);
+    constexpr int kStages = 12;
+    static_assert(kStages <= NB - 2, "one stage per column update");
+#pragma unroll
+    for (int i = 0; i < kStages; ++i) stage(i, 0);
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
         if (q < jb) {
-            const int ps = uniform_i(p >> 6), pl = uniform_i(p & 63);
             double pj[NB];
 #pragma unroll
             for (int s = 0; s < NR; ++s)
@@ -479,27 +517,31 @@ __device__ __forceinline__ bool panel_big(const BigLds &L, int kb, int jb, bool 
                     for (int j = 0; j < NB; ++j) pj[j] = readlane_d(a[s][j], pl);
                 }
             const double r = rinv;
-            ok = ok && fabs(r) < INFINITY;
-            double m[NR];
+            ok = ok && v != 0u && fabs(r) < INFINITY;   // v = 0: no free row with a nonzero entry
+            double m[NR];   // minus the multiplier
 #pragma unroll
             for (int s = 0; s < NR; ++s) {
                 const bool mine = ps == s && lane == pl;
-                m[s] = mine ? 0.0 : a[s][q] * r;
-                a[s][q] = mine ? 1.0 : -m[s];
+                m[s] = a[s][q] * -r;
+                a[s][q] = mine ? 1.0 : m[s];
+                m[s] = mine ? 0.0 : m[s];
                 rs[s] = mine ? r : rs[s];
                 st[s] = mine ? kb + q : st[s];
                 fr[s] = fr[s] && !mine;
             }
             if (q + 1 < NB) {
 #pragma unroll
-                for (int s = 0; s < NR; ++s) a[s][q + 1] = fma(-m[s], pj[q + 1], a[s][q + 1]);
-                search(q + 1);
+                for (int s = 0; s < NR; ++s) a[s][q + 1] = fma(m[s], pj[q + 1], a[s][q + 1]);
             }
+            int i = 0;
 #pragma unroll
             for (int j = 0; j < NB; ++j)
                 if (j != q && j != q + 1) {
+                    if (q + 1 < NB && i < kStages) stage(i, q + 1);
+                    ++i;
 #pragma unroll
-                    for (int s = 0; s < NR; ++s) a[s][j] = fma(-m[s], pj[j], a[s][j]);
+                    for (int s = 0; s < NR; ++s) a[s][j] = fma(m[s], pj[j], a[s][j]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
         }
     }
@@ -619,32 +661,53 @@ __device__ __forceinline__ double solve_big(const BigLds &L, double b) {
     double x = act ? b : 0.0;
     if (act && half == 0 && st < NB) v[st] = x;
     double r[8];
+    const bool busy = uniform_i(tid & ~63) < 2 * n;   // wavefronts past the rows only wait
+    if (busy) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = row[i];
+        for (int i = 0; i < 8; ++i) r[i] = row[i];
+    }
     __syncthreads();
-    for (int kb = 0; kb < n; kb += NB) {
-        const int jb = n - kb - 8 * half;   // this half's columns, if the panel is the last
-        double s0 = 0.0, s1 = 0.0;
+    int kb = 0;
+    for (; kb + NB < n; kb += NB) {
+        if (busy) {
+            const double *vk = v + kb + 8 * half;
+            double w[8];
 #pragma unroll
-        for (int i = 0; i < 8; i += 2) {
-            const double v0 = i < jb ? v[kb + 8 * half + i] : 0.0;
-            const double v1 = i + 1 < jb ? v[kb + 8 * half + i + 1] : 0.0;
-            s0 = fma(i < jb ? r[i] : 0.0, v0, s0);
-            s1 = fma(i + 1 < jb ? r[i + 1] : 0.0, v1, s1);
-        }
-        double s = s0 + s1;
-        s += dpp_d<0xB1>(s);
-        if ((unsigned)(st - kb) >= (unsigned)NB) x += s;
-        if (kb + NB < n) {
+            for (int i = 0; i < 8; ++i) w[i] = vk[i];
+            double s0 = r[0] * w[0], s1 = r[1] * w[1];
+#pragma unroll
+            for (int i = 2; i < 8; i += 2) {
+                s0 = fma(r[i], w[i], s0);
+                s1 = fma(r[i + 1], w[i + 1], s1);
+            }
+            double s = s0 + s1;
+            s += dpp_d<0xB1>(s);
+            if ((unsigned)(st - kb) >= (unsigned)NB) x += s;
             const int kn = kb + NB;
             if (act && half == 0 && (unsigned)(st - kn) < (unsigned)NB) v[st] = x;
+            if (kn + NB <= n) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) r[i] = kn + 8 * half + i < n ? row[kn + i] : 0.0;
-        } else if (act && half == 0) {
-            vf[st] = x;
+                for (int i = 0; i < 8; ++i) r[i] = row[kn + i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) r[i] = kn + 8 * half + i < n ? row[kn + i] : 0.0;
+            }
         }
         __syncthreads();
     }
+    if (busy) {
+        // the last panel, up to 16 columns
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int c = kb + 8 * half + i;
+            s = fma(r[i], c < n ? v[c] : 0.0, s);
+        }
+        s += dpp_d<0xB1>(s);
+        if ((unsigned)(st - kb) >= (unsigned)NB) x += s;
+        if (act && half == 0) vf[st] = x;
+    }
+    __syncthreads();
     // unknown own = kb + q: row prow[own] of D in the panel's columns
     double s = 0.0;
     if (act) {
@@ -662,9 +725,8 @@ __device__ __forceinline__ double solve_big(const BigLds &L, double b) {
 // One Rodas4 attempt of size h from y with f0 = f(y) and M in L.A; false when
 // M is singular.
 template <int NR>
-__device__ __forceinline__ bool rodas_attempt_big(const MechDev *__restrict__ M, const BigLds &L, const Species &S,
-                                                  double p, double y, double f0, double h, double &ynew,
-                                                  double &err) {
+__device__ __forceinline__ bool rodas_attempt_big(const MechDev *__restrict__ M, const BigLds &L, double p,
+                                                  double y, double f0, double h, double &ynew, double &err) {
     if (!gj_big<NR>(L)) return false;
     const double hinv = 1.0 / h;
     double u[6] = {0, 0, 0, 0, 0, 0};
@@ -676,7 +738,7 @@ __device__ __forceinline__ bool rodas_attempt_big(const MechDev *__restrict__ M,
             ys = y;
 #pragma unroll
             for (int j = 0; j < 5; ++j) ys += kBigA[s][j] * u[j];
-            rv = rhs_big<false, false>(M, p, ys, S, 0.0, L);
+            rv = rhs_big<false, false>(M, p, ys, 0.0, L);
 #pragma unroll
             for (int j = 0; j < 5; ++j) rv += (kBigC[s][j] * hinv) * u[j];
         }
@@ -697,7 +759,7 @@ __device__ __forceinline__ double load_unknown(const IntParams &P, int64_t cell,
 // Adaptive integration of one cell; control logic of the wavefront kernel.
 template <int NR>
 __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParams &P, int64_t cell,
-                                   const BigLds &L, const Species &S) {
+                                   const BigLds &L) {
     const int tid = threadIdx.x, own = tid >> 1;
     const int n = M->n, N = M->N;
     const double dt = P.dt;
@@ -728,9 +790,9 @@ __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParam
         if (h >= dt - t) { h = dt - t; last = true; }
         if (h < P.hmin_frac * dt) { status = 2; break; }
         // f and the Jacobian of y, assembled as the matrix of this step size
-        const double f0 = rhs_big<true, true>(M, p, y, S, 1.0 / (kBigGamma * h), L);
+        const double f0 = rhs_big<true, true>(M, p, y, 1.0 / (kBigGamma * h), L);
         double ynew = 0.0, ev = 0.0;
-        const bool ok = rodas_attempt_big<NR>(M, L, S, p, y, f0, h, ynew, ev);
+        const bool ok = rodas_attempt_big<NR>(M, L, p, y, f0, h, ynew, ev);
         // largest scaled error; a NaN counts as infinite (both shrink by 0.2)
         double e = INFINITY;
         if (ok) {
@@ -779,7 +841,6 @@ template <int NR>
 __global__ __launch_bounds__(BT) void k_big_plain(const MechDev *__restrict__ M, IntParams P) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const Species S = load_species(M);
     // round robin over the slots, or (block_static) one contiguous block each
     const int64_t B = (P.ncells + gridDim.x - 1) / gridDim.x;
     const int64_t c0 = P.block_static ? blockIdx.x * B : blockIdx.x;
@@ -787,7 +848,7 @@ __global__ __launch_bounds__(BT) void k_big_plain(const MechDev *__restrict__ M,
     const int64_t stride = P.block_static ? 1 : gridDim.x;
     for (int64_t cell = c0; cell < c1; cell += stride) {
         if (P.flags && P.flags[cell] >= 2) continue;
-        integrate_cell_big<NR>(M, P, cell, L, S);
+        integrate_cell_big<NR>(M, P, cell, L);
     }
 }
 
@@ -796,7 +857,6 @@ template <int NR>
 __global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M, IntParams P) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const Species S = load_species(M);
     const int nact = *P.n_active;
     const int chunk = P.chunk;
     int seg = blockIdx.x % NSEG;
@@ -819,7 +879,7 @@ __global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M,
         for (int q = 0; q < chunk; ++q) {
             const int pos = first + NSEG * q;
             if (pos >= nact) break;
-            integrate_cell_big<NR>(M, P, P.queue[pos], L, S);
+            integrate_cell_big<NR>(M, P, P.queue[pos], L);
         }
     }
 }
@@ -829,11 +889,10 @@ __global__ __launch_bounds__(BT) void k_big_rhs_jac(const MechDev *__restrict__ 
                                                     double *fout, double *Jout) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const Species S = load_species(M);
     const int64_t cell = blockIdx.x;
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
-    const double f = rhs_big<true, false>(M, P.p[cell], y, S, 0.0, L);
+    const double f = rhs_big<true, false>(M, P.p[cell], y, 0.0, L);
     if (fout && own < n && (tid & 1) == 0) fout[cell * n + own] = f;
     if (Jout)
         for (int i = tid; i < n * n; i += BT)
@@ -845,14 +904,13 @@ __global__ __launch_bounds__(BT) void k_big_rodas_step(const MechDev *__restrict
                                                        double h, double *ynew_out, double *err_out) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const Species S = load_species(M);
     const int64_t cell = blockIdx.x;
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
     const double p = P.p[cell];
-    const double f0 = rhs_big<true, true>(M, p, y, S, 1.0 / (kBigGamma * h), L);
+    const double f0 = rhs_big<true, true>(M, p, y, 1.0 / (kBigGamma * h), L);
     double ynew = 0.0, err = 0.0;
-    const bool ok = rodas_attempt_big<NR>(M, L, S, p, y, f0, h, ynew, err);
+    const bool ok = rodas_attempt_big<NR>(M, L, p, y, f0, h, ynew, err);
     if (!ok) { ynew = NAN; err = NAN; }
     if (own < n && (tid & 1) == 0) {
         ynew_out[cell * n + own] = ynew;
