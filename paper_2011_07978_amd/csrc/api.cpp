@@ -716,17 +716,8 @@ int chem_set_mechanism(chem_ctx *c, const chem_mech_desc *m) {
         free_mech(c);
         return rc;
     }
-    // LDS layout (doubles)
-    int off = 0;
-    M.off_q = off; off += N + 1;   // production rates (+ sentinel)
-    M.off_C = off; off += N + 1;
-    M.off_g = off; off += N + 1;    // exp(g_k) RT/p_atm (+ sentinel 1)
-    M.off_gi = off; off += N + 1;   // its reciprocal (+ sentinel 1)
-    M.off_h = off; off += N + 1;
-    M.off_e = off; off += N;
-    M.off_cp = off; off += N;
-    M.off_tb = off; off += M.n;
-    M.lds_doubles = off;
+    // wavefront kernel: eight arrays of one padded row each per wavefront
+    M.lds_doubles = 8 * std::max(0, pick_np(M.n));
     {
         std::vector<MechDev> one(1, M);
         const MechDev *dm = nullptr;

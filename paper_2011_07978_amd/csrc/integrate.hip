@@ -38,14 +38,14 @@ namespace chem {
 // Rodas4, Hairer & Wanner, Solving ODEs II, Sec. IV.7, transformed form:
 // (I/(gamma h) - J) u_i = f(y + sum_j a_ij u_j) + sum_j (c_ij / h) u_j.
 // Row 5 of A is the stage-6 input (a_5j, then 1 for u_5).
-static __constant__ double kRodasA[6][6] = {
+static constexpr double kRodasA[6][6] = {
     {0, 0, 0, 0, 0, 0},
     {1.544, 0, 0, 0, 0, 0},
     {0.9466785280815826, 0.2557011698983284, 0, 0, 0, 0},
     {3.314825187068521, 2.896124015972201, 0.9986419139977817, 0, 0, 0},
     {1.221224509226641, 6.019134481288629, 12.53708332932087, -0.6878860361058950, 0, 0},
     {1.221224509226641, 6.019134481288629, 12.53708332932087, -0.6878860361058950, 1.0, 0}};
-static __constant__ double kRodasC[6][6] = {
+static constexpr double kRodasC[6][6] = {
     {0, 0, 0, 0, 0, 0},
     {-5.6688, 0, 0, 0, 0, 0},
     {-2.430093356833875, -0.2063599157091915, 0, 0, 0, 0},
@@ -73,13 +73,29 @@ __device__ __forceinline__ void wave_sync() {
 
 extern __shared__ double lds_all[];
 
-// The workgroup's LDS copy of the records is field-major: field f of species
-// k at f N + k, field f of reaction j at N SPC_STRIDE + f R + j (a reaction
-// record is 8 doubles, its four index words packed two per double), so the
-// lanes of a wavefront, each on its own species or reaction, read
-// consecutive doubles.
+// The workgroup's LDS copy of the records is in pairs of doubles: pair q of
+// species k (fields 2q, 2q + 1 of its record) at 2 (q N + k), pair q of reaction
+// j at N SPC_STRIDE + 2 (q R + j), so the lanes of a wavefront, each on its own
+// species or reaction, read consecutive 16-byte pairs, one instruction each.
+// A reaction's pairs are (ln A, b), (Ea/R, idx[0..1]), (idx[2..3], eff[0]) and
+// (eff[1], eff[2]); only third-body reactions read the last.
 constexpr int RXN_FIELDS = (int)(sizeof(RxnRec) / sizeof(double));
 static_assert(RXN_FIELDS == 8, "reaction record of 8 doubles");
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+// place of field f of a reaction record (ln A, b, Ea/R, eff[3], idx pairs) in
+// that order of pairs
+__device__ __forceinline__ int rxn_place(int f) {
+    return f < 3 ? f : f == 6 ? 3 : f == 7 ? 4 : f + 2;
+}
+
+// The wavefront's small region: eight arrays of NP doubles at fixed distances,
+// so that one address serves an index in all of them.
+//   omega (production rates, + sentinel), C, exp(g) RT/p_atm and its
+//   reciprocal, H/RT (all + sentinel), and for the Jacobian e, cp, tb
+template <int NP>
+struct Small {
+    static constexpr int w = 0, C = NP, g = 2 * NP, gi = 3 * NP, h = 4 * NP, e = 5 * NP, cp = 6 * NP, tb = 7 * NP;
+};
 
 __host__ __device__ inline int table_doubles(const MechDev &M) {
     return M.N * SPC_STRIDE + M.R * RXN_FIELDS;
@@ -159,51 +175,64 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     const MechDev &M = *Mp;
     int N = M.N, R = M.R, n = M.n, ldj = M.ldj;
     asm volatile("" : "+s"(N), "+s"(R), "+s"(n), "+s"(ldj));
-    double *__restrict__ wl = lds + M.off_q;    // production rates omega_k (+ sentinel)
-    double *__restrict__ Cl = lds + M.off_C;
-    double *__restrict__ gl = lds + M.off_g;
-    double *__restrict__ gil = lds + M.off_gi;
-    double *__restrict__ hl = lds + M.off_h;
-    double *__restrict__ el = lds + M.off_e;
-    double *__restrict__ cpl = lds + M.off_cp;
-    double *__restrict__ tbl = lds + M.off_tb;
+    using SM = Small<NP>;
+    double *__restrict__ wl = lds + SM::w;
+    double *__restrict__ Cl = lds + SM::C;
+    double *__restrict__ gl = lds + SM::g;
+    double *__restrict__ gil = lds + SM::gi;
+    double *__restrict__ hl = lds + SM::h;
+    double *__restrict__ el = lds + SM::e;
+    double *__restrict__ cpl = lds + SM::cp;
+    double *__restrict__ tbl = lds + SM::tb;
 
     const double T = readlane_d(y, 0);
-    const double lnT = log(T);
+    const double lnT = log_pos(T);
     const double ln_patm_RT = kLnPatmRu - lnT;   // ln(p_atm / (R T))
-    const double invT = 1.0 / T;
+    const double invT = recip_nr(T);
     const bool sp = lane >= 1 && lane <= N;
     const int k = sp ? lane - 1 : 0;
 
     // species thermo (NASA-7 single range), Horner form
     double cpR = 0.0, hRT = 0.0, gRT = 0.0, dcpR = 0.0, invWk = 0.0, Wk = 0.0;
     if (sp) {
-        const double *a = LT ? lds_all + k : (const double *)(gbl(M.spc) + k * SPC_STRIDE);
-        const int fs = LT ? N : 1;   // distance between fields
-        const double a1 = a[0], a2 = a[fs], a3 = a[2 * fs], a4 = a[3 * fs], a5 = a[4 * fs];
-        const double a6 = a[5 * fs], a7 = a[6 * fs];
-        const double h2 = a[7 * fs], h3 = a[8 * fs], h4 = a[9 * fs], h5 = a[10 * fs];
-        const double s3 = a[11 * fs], s4 = a[12 * fs], s5 = a[13 * fs];
+        double rec[16];
+        if (LT) {
+            const f64x2 *a = reinterpret_cast<const f64x2 *>(lds_all) + k;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const f64x2 v = a[q * N];
+                rec[2 * q] = v.x;
+                rec[2 * q + 1] = v.y;
+            }
+        } else {
+            const auto *a = gbl(M.spc) + k * SPC_STRIDE;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) rec[q] = a[q];
+        }
+        const double a1 = rec[0], a2 = rec[1], a3 = rec[2], a4 = rec[3], a5 = rec[4], a6 = rec[5], a7 = rec[6];
+        const double h2 = rec[7], h3 = rec[8], h4 = rec[9], h5 = rec[10];
+        const double s3 = rec[11], s4 = rec[12], s5 = rec[13];
         cpR = a1 + T * (a2 + T * (a3 + T * (a4 + T * a5)));
         hRT = a1 + T * (h2 + T * (h3 + T * (h4 + T * h5))) + a6 * invT;
         const double sR = a1 * lnT + T * (a2 + T * (s3 + T * (s4 + T * s5))) + a7;
         gRT = hRT - sR;
         if (JAC) dcpR = a2 + T * (2.0 * a3 + T * (3.0 * a4 + T * (4.0 * a5)));
-        Wk = a[14 * fs];
-        invWk = a[15 * fs];
+        Wk = rec[14];
+        invWk = rec[15];
     }
     const double yw = sp ? y * invWk : 0.0;
     const double sumYW = species_sum<NP>(yw);
-    const double rho = p / (RU_ERG * T * sumYW);
-    const double irho = (RU_ERG * T * sumYW) / p;
+    const double pv = RU_ERG * T * sumYW;
+    const double rho = p * recip_nr(pv);
+    const double irho = pv * recip_nr(p);
     const double Ctot = rho * sumYW;
     if (sp) {
         Cl[k] = rho * yw;
         // species factors of the equilibrium constant: a reaction's
         // 1 / K_c = prod_products E_k / prod_reactants E_k, E_k = exp(g_k) RT / p_atm
         const double gx = gRT - ln_patm_RT;
-        gl[k] = exp(gx);
-        gil[k] = exp(-gx);
+        gl[k] = exp_d(gx);
+        gil[k] = exp_d(-gx);
         if (JAC) {
             hl[k] = hRT;
             el[k] = hRT * invWk;
@@ -221,23 +250,20 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     // their reactant and product slots (LDS float atomics; missing slots hit
     // the sentinel entry N)
     const double lnp = FO ? log(p) : 0.0;
-    const double *rtab = lds_all + N * SPC_STRIDE;
+    const f64x2 *rtab = reinterpret_cast<const f64x2 *>(lds_all + N * SPC_STRIDE);
     const RxnRec *rxn = (const RxnRec *)gbl(M.rxn);
-    auto reaction = [&](const int j, const bool valid) {
+    auto reaction = [&](const int j) {
         RxnRec rec;
         if (LT) {
-            const double *r = rtab + j;
-            rec.lnA = r[0];
-            rec.b = r[R];
-            rec.EaR = r[2 * R];
-            rec.eff[0] = r[3 * R];
-            rec.eff[1] = r[4 * R];
-            rec.eff[2] = r[5 * R];
-            const double w01 = r[6 * R], w23 = r[7 * R];
-            rec.idx[0] = __double2loint(w01);
-            rec.idx[1] = __double2hiint(w01);
-            rec.idx[2] = __double2loint(w23);
-            rec.idx[3] = __double2hiint(w23);
+            const f64x2 v0 = rtab[j], v1 = rtab[R + j], v2 = rtab[2 * R + j];
+            rec.lnA = v0.x;
+            rec.b = v0.y;
+            rec.EaR = v1.x;
+            rec.idx[0] = __double2loint(v1.y);
+            rec.idx[1] = __double2hiint(v1.y);
+            rec.idx[2] = __double2loint(v2.x);
+            rec.idx[3] = __double2hiint(v2.x);
+            rec.eff[0] = v2.y;
         } else {
             rec = rxn[j];
         }
@@ -253,12 +279,24 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         double lnAj = rec.lnA, bj = rec.b, EaRj = rec.EaR;
         if (FO && (tbw & TB_PLOG)) plog_arrhenius(M.plog + (size_t)j * PLOG_STRIDE, lnp, lnAj, bj, EaRj);
         const double ln_kf = lnAj + bj * lnT - EaRj * invT;
-        const double kf = exp(ln_kf);
+        const double kf = exp_d(ln_kf);
         const double kr = kf * ((gl[p0] * gil[r0]) * (gl[p1] * gil[r1]) * gl[p2]);
         const double Pf = Cr0 * Cr1;
         const double Pr = Cp0 * Cp1 * Cp2;
-        const double e0v = rec.eff[0], e1v = rec.eff[1], e2v = rec.eff[2];
-        double m = tb == TB_NONE ? 1.0 : Ctot + e0v * Cl[es0] + e1v * Cl[es1] + e2v * Cl[es2];
+        double m = 1.0;
+        const double e0v = rec.eff[0];
+        double e1v = 0.0, e2v = 0.0;
+        if (tb != TB_NONE) {
+            if (LT) {
+                const f64x2 v3 = rtab[3 * R + j];
+                e1v = v3.x;
+                e2v = v3.y;
+            } else {
+                e1v = rec.eff[1];
+                e2v = rec.eff[2];
+            }
+            m = Ctot + e0v * Cl[es0] + e1v * Cl[es1] + e2v * Cl[es2];
+        }
         if (tb >= TB_LIST0) {
             const int e1 = M.tb_ptr[tb - TB_LIST0 + 1];
             for (int e = M.tb_ptr[tb - TB_LIST0]; e < e1; ++e) m += M.eff_am1[e] * Cl[M.eff_sp[e]];
@@ -271,7 +309,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
                          bj * invT + EaRj * invT * invT, m, G, dGdM, dlnGdT);
             m = G;
         }
-        const double Delta = valid ? kf * Pf - kr * Pr : 0.0;
+        const double Delta = kf * Pf - kr * Pr;
         const double q = m * Delta;
         lds_add(wl + r0, -q);
         lds_add(wl + r1, -q);
@@ -282,7 +320,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
             const double dlnkf = bj * invT + EaRj * invT * invT + dlnGdT;
             const double dH = -hl[r0] - hl[r1] + hl[p0] + hl[p1] + hl[p2];
             const double dlnkr = dlnkf - (dH - snu) * invT;
-            const double mkf = valid ? m * kf : 0.0, mkr = valid ? m * kr : 0.0;
+            const double mkf = m * kf, mkr = m * kr;
             const double dqdT = mkf * dlnkf * Pf - mkr * dlnkr * Pr;
             const int sl[5] = {r0, r1, p0, p1, p2};
             const double ds[5] = {mkf * Cr1, mkf * Cr0, -mkr * Cp1 * Cp2, -mkr * Cp0 * Cp2,
@@ -316,20 +354,20 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     // wavefront covers this one's load, exp and LDS latencies, and the
     // smaller loop body keeps registers free
 #pragma unroll 1
-    for (int j = lane; j < R; j += 64) reaction(j, true);
+    for (int j = lane; j < R; j += 64) reaction(j);
     wave_sync();
 
     // species: dY_k/dt = W_k omega_k / rho; dT/dt = -sum_k H_k omega_k / (rho cp)
     const double fk = sp ? Wk * wl[k] * irho : 0.0;
     const double hs = species_sum<NP>(sp ? hRT * invWk * fk : 0.0);
     const double cps = species_sum<NP>(sp ? y * cpR * invWk : 0.0);
-    const double icps = 1.0 / cps;
+    const double icps = recip_nr(cps);
     const double fT = -T * hs * icps;
 
     if (JAC) {
         const double cpf = species_sum<NP>(sp ? cpR * invWk * fk : 0.0);
         const double dcps = species_sum<NP>(sp ? y * dcpR * invWk : 0.0);
-        const double Wbar = 1.0 / sumYW;
+        const double Wbar = recip_nr(sumYW);
         // species rows: chain rule from concentrations to (T, Y)
         if (sp) {
             double *row = Jl + lane * ldj;
@@ -348,7 +386,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
                 // 1/W_i from the species records in the shared table (broadcast reads)
 #pragma unroll 8
                 for (int i = 0; i < N; ++i)
-                    row[1 + i] = lds_all[15 * N + i] * (Wk * (row[1 + i] + tbk) + cst);
+                    row[1 + i] = lds_all[2 * (7 * N + i) + 1] * (Wk * (row[1 + i] + tbk) + cst);
             } else {
                 const auto *iw = gbl(M.invW);
 #pragma unroll 8
@@ -576,30 +614,45 @@ __device__ __forceinline__ bool rodas_attempt(const MechDev *__restrict__ M, dou
     if (!ok) return false;
     const double hinv = 1.0 / h;
     double u0 = 0.0, u1 = 0.0, u2 = 0.0, u3 = 0.0, u4 = 0.0, u5 = 0.0, ys = y;
+    // one copy of the RHS and the solve for all stages; the combinations
+    // before and after them branch on the stage, whose terms are the stage's
+    // own (u_j, j < s)
 #pragma unroll 1
     for (int s = 0; s < 6; ++s) {
         double rv = f0;
         if (s > 0) {
             ys = y;
-            ys += kRodasA[s][0] * u0;
-            ys += kRodasA[s][1] * u1;
-            ys += kRodasA[s][2] * u2;
-            ys += kRodasA[s][3] * u3;
-            ys += kRodasA[s][4] * u4;
+            switch (s) {
+#define STAGE_Y(i, j) ys = fma(kRodasA[i][j], u##j, ys);
+                case 1: STAGE_Y(1, 0) break;
+                case 2: STAGE_Y(2, 0) STAGE_Y(2, 1) break;
+                case 3: STAGE_Y(3, 0) STAGE_Y(3, 1) STAGE_Y(3, 2) break;
+                case 4: STAGE_Y(4, 0) STAGE_Y(4, 1) STAGE_Y(4, 2) STAGE_Y(4, 3) break;
+                default: STAGE_Y(5, 0) STAGE_Y(5, 1) STAGE_Y(5, 2) STAGE_Y(5, 3) STAGE_Y(5, 4) break;
+#undef STAGE_Y
+            }
             rv = rhs_eval<NP, false, LT, FO>(M, p, ys, lds, nullptr);
-            rv += (kRodasC[s][0] * hinv) * u0;
-            rv += (kRodasC[s][1] * hinv) * u1;
-            rv += (kRodasC[s][2] * hinv) * u2;
-            rv += (kRodasC[s][3] * hinv) * u3;
-            rv += (kRodasC[s][4] * hinv) * u4;
+            double cu = 0.0;
+            switch (s) {
+#define STAGE_C(i, j) cu = fma(kRodasC[i][j], u##j, cu);
+                case 1: STAGE_C(1, 0) break;
+                case 2: STAGE_C(2, 0) STAGE_C(2, 1) break;
+                case 3: STAGE_C(3, 0) STAGE_C(3, 1) STAGE_C(3, 2) break;
+                case 4: STAGE_C(4, 0) STAGE_C(4, 1) STAGE_C(4, 2) STAGE_C(4, 3) break;
+                default: STAGE_C(5, 0) STAGE_C(5, 1) STAGE_C(5, 2) STAGE_C(5, 3) STAGE_C(5, 4) break;
+#undef STAGE_C
+            }
+            rv = fma(hinv, cu, rv);
         }
         const double us = gj_solve<NP>(a, dinv, pk, rv);
-        u0 = s == 0 ? us : u0;
-        u1 = s == 1 ? us : u1;
-        u2 = s == 2 ? us : u2;
-        u3 = s == 3 ? us : u3;
-        u4 = s == 4 ? us : u4;
-        u5 = s == 5 ? us : u5;
+        switch (s) {
+            case 0: u0 = us; break;
+            case 1: u1 = us; break;
+            case 2: u2 = us; break;
+            case 3: u3 = us; break;
+            case 4: u4 = us; break;
+            default: u5 = us; break;
+        }
     }
     ynew = ys + u5;
     err = u5;
@@ -613,7 +666,7 @@ __device__ __forceinline__ bool rodas_attempt(const MechDev *__restrict__ M, dou
 // shared table (once per launch), and the LDS is [table][locks][jslots
 // Jacobian slots][one small region per wavefront]; jslots <= 0 or >= the
 // wavefronts of the workgroup gives every wavefront a private slot.
-template <bool LT>
+template <int NP, bool LT>
 __device__ __forceinline__ double *init_lds(const MechDev *Mp, int jslots, JacSlot &js) {
     const MechDev &M = *Mp;
     const int jd = M.n * M.ldj;
@@ -633,10 +686,12 @@ __device__ __forceinline__ double *init_lds(const MechDev *Mp, int jslots, JacSl
         const double *rxd = reinterpret_cast<const double *>(M.rxn);
         for (int i = threadIdx.x; i < ns; i += blockDim.x) {
             const int k = i / SPC_STRIDE, f = i - k * SPC_STRIDE;
-            lds_all[f * M.N + k] = spc[i];
+            lds_all[2 * ((f >> 1) * M.N + k) + (f & 1)] = spc[i];
         }
-        for (int i = threadIdx.x; i < nr; i += blockDim.x)
-            lds_all[ns + (i & (RXN_FIELDS - 1)) * M.R + (i / RXN_FIELDS)] = gbl(rxd)[i];
+        for (int i = threadIdx.x; i < nr; i += blockDim.x) {
+            const int f = rxn_place(i & (RXN_FIELDS - 1));
+            lds_all[ns + 2 * ((f >> 1) * M.R + i / RXN_FIELDS) + (f & 1)] = gbl(rxd)[i];
+        }
         int *locks = reinterpret_cast<int *>(lds_all + ns + nr);
         const bool priv = jslots <= 0 || jslots >= wpb;
         const int nslot = priv ? wpb : jslots;
@@ -650,10 +705,10 @@ __device__ __forceinline__ double *init_lds(const MechDev *Mp, int jslots, JacSl
         lds = pool + (size_t)nslot * jd + (size_t)w * M.lds_doubles;
     }
     if (lane_id() == 0) {
-        lds[M.off_C + M.N] = 1.0;
-        lds[M.off_g + M.N] = 1.0;
-        lds[M.off_gi + M.N] = 1.0;
-        lds[M.off_h + M.N] = 0.0;
+        lds[Small<NP>::C + M.N] = 1.0;
+        lds[Small<NP>::g + M.N] = 1.0;
+        lds[Small<NP>::gi + M.N] = 1.0;
+        lds[Small<NP>::h + M.N] = 0.0;
     }
     wave_sync();
     return lds;
@@ -764,7 +819,7 @@ __device__ __forceinline__ void integrate_cell(const MechDev *__restrict__ M, co
 template <int NP, bool FO>
 __global__ __launch_bounds__(64) void k_integrate_plain(const MechDev *__restrict__ M, IntParams P) {
     JacSlot js;
-    double *lds = init_lds<false>(M, 0, js);
+    double *lds = init_lds<NP, false>(M, 0, js);
     const int64_t cell = blockIdx.x;
     if (P.flags && P.flags[cell] >= 2) return;
     integrate_cell<NP, false, FO>(M, P, cell, lds, js);
@@ -783,7 +838,7 @@ template <int NP, bool FO>
 __global__ __launch_bounds__(64 * max_wpb(NP)) void k_integrate_queue(const MechDev *__restrict__ M,
                                                                       IntParams P) {
     JacSlot js;
-    double *lds = init_lds<true>(M, P.jslots, js);
+    double *lds = init_lds<NP, true>(M, P.jslots, js);
     const int wpb = (int)(blockDim.x >> 6);
     const int wave = (int)blockIdx.x * wpb + (int)(threadIdx.x >> 6);
     // P.block_static: wavefront w owns cells [w B, (w + 1) B) and integrates
@@ -834,7 +889,7 @@ template <int NP>
 __global__ __launch_bounds__(64) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
                                                      double *fout, double *Jout) {
     JacSlot js;
-    double *lds = init_lds<true>(M, 0, js);
+    double *lds = init_lds<NP, true>(M, 0, js);
     const int64_t cell = blockIdx.x;
     const int lane = lane_id(), n = M->n, N = M->N;
     double y = 0.0;
@@ -851,7 +906,7 @@ template <int NP>
 __global__ __launch_bounds__(64) void k_rodas_step(const MechDev *__restrict__ M, IntParams P,
                                                    double h, double *ynew_out, double *err_out) {
     JacSlot js;
-    double *lds = init_lds<true>(M, 0, js);
+    double *lds = init_lds<NP, true>(M, 0, js);
     const int64_t cell = blockIdx.x;
     const int lane = lane_id(), n = M->n, N = M->N;
     double y = 0.0;

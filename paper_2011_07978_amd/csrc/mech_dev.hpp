@@ -125,9 +125,7 @@ struct MechDev {
     const double *fo;       // [R][FO_STRIDE] fall-off parameters by reaction slot
     const double *plog;     // [R][PLOG_STRIDE] PLOG tables by reaction slot
     int has_fo;             // any fall-off or PLOG reaction
-    // per-wavefront LDS region (offsets in doubles); the Jacobian (n rows of
-    // stride ldj) has a slot of its own
-    int off_q, off_C, off_g, off_gi, off_h, off_e, off_cp, off_tb, lds_doubles;
+    int lds_doubles;        // wavefront kernel: per-wavefront LDS region besides the Jacobian slot
 };
 
 struct IntParams {

@@ -117,6 +117,53 @@ __device__ __forceinline__ double recip_nr(double x) {
     return fma(r, e, r);
 }
 
+// exp(x): x = n ln 2 + r with |r| <= ln 2 / 2, exp(r) = 1 + r + r^2 q(r) with q
+// the minimax polynomial of degree 9 (relative error 3.6e-18), scaled by 2^n.
+// 19 vector instructions against about 40 of the library's; within an ulp.
+// Arguments beyond the range of doubles give 0 or infinity; NaN counts as out
+// of range (a state with a NaN is NaN through its concentrations).
+__device__ __forceinline__ double exp_d(double x) {
+    x = fmin(fmax(x, -1100.0), 1100.0);
+    const double n = rint(x * 1.4426950408889634);
+    double r = fma(-n, 0.6931471805599453, x);
+    r = fma(-n, 2.3190468138462996e-17, r);
+    double q = fma(r, 2.5000006698683492e-08, 2.763025572227658e-07);
+    q = fma(r, q, 2.7557586572016356e-06);
+    q = fma(r, q, 2.4801493081083114e-05);
+    q = fma(r, q, 0.0001984126950633851);
+    q = fma(r, q, 0.001388888894364476);
+    q = fma(r, q, 0.008333333333494577);
+    q = fma(r, q, 0.041666666666530114);
+    q = fma(r, q, 0.16666666666666413);
+    q = fma(r, q, 0.5000000000000011);
+    q = fma(r, q, 1.0);
+    return ldexp(fma(r, q, 1.0), (int)n);
+}
+
+// log(x) for x > 0, NaN otherwise: x = 2^e m with m in [sqrt(1/2), sqrt(2)),
+// s = (m - 1) / (m + 1), log m = 2 s + s^3 P(s^2) with P the minimax
+// polynomial of degree 6 (relative error 1.2e-18).  For temperatures (e >= 5)
+// within an ulp; near x = 1 the error is absolute, about 1e-16.
+__device__ __forceinline__ double log_pos(double x) {
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool lowhalf = m < 0.7071067811865476;
+    m = ldexp(m, lowhalf ? 1 : 0);
+    e = lowhalf ? e - 1 : e;
+    const double s = (m - 1.0) * recip_nr(m + 1.0);
+    const double z = s * s;
+    double q = fma(z, 0.14796756087565172, 0.15313973862241478);
+    q = fma(z, q, 0.18183567166832199);
+    q = fma(z, q, 0.22222198521620765);
+    q = fma(z, q, 0.28571428742859334);
+    q = fma(z, q, 0.39999999999412694);
+    q = fma(z, q, 0.6666666666666735);
+    const double d = (double)e;
+    const double lo = fma(d, 2.3190468138462996e-17, s * (z * q));
+    const double l = fma(d, 0.6931471805599453, fma(2.0, s, lo));
+    return x > 0.0 ? l : __builtin_nan("");
+}
+
 // Lane mask of p (the compiler's own mask, with no detour through an integer).
 __device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
