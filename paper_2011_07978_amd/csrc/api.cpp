@@ -716,8 +716,8 @@ int chem_set_mechanism(chem_ctx *c, const chem_mech_desc *m) {
         free_mech(c);
         return rc;
     }
-    // wavefront kernel: eight arrays of one padded row each per wavefront
-    M.lds_doubles = 8 * std::max(0, pick_np(M.n));
+    // wavefront kernel: six arrays of one padded row each per wavefront
+    M.lds_doubles = 6 * std::max(0, pick_np(M.n));
     {
         std::vector<MechDev> one(1, M);
         const MechDev *dm = nullptr;

@@ -26,10 +26,14 @@
 // rates), and a pool of Jacobian slots smaller than the number
 // of wavefronts.  A wavefront holds a slot only from the Jacobian's assembly
 // until the iteration matrix has been built in its registers; after a
-// rejected step it assembles the (identical) Jacobian again.  This keeps
+// rejected step (about 1 % of them) it assembles the (identical) Jacobian
+// again.  This keeps
 // eight wavefronts, two per SIMD, on a CU for the 53-species mechanism.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <algorithm>
+
 #include "mech_dev.hpp"
 #include "wave.hpp"
 
@@ -88,13 +92,14 @@ __device__ __forceinline__ int rxn_place(int f) {
     return f < 3 ? f : f == 6 ? 3 : f == 7 ? 4 : f + 2;
 }
 
-// The wavefront's small region: eight arrays of NP doubles at fixed distances,
+// The wavefront's small region: six arrays of NP doubles at fixed distances,
 // so that one address serves an index in all of them.
 //   omega (production rates, + sentinel), C, exp(g) RT/p_atm and its
-//   reciprocal, H/RT (all + sentinel), and for the Jacobian e, cp, tb
+//   reciprocal, H/RT (all + sentinel), and for the Jacobian the third bodies'
+//   derivative per row
 template <int NP>
 struct Small {
-    static constexpr int w = 0, C = NP, g = 2 * NP, gi = 3 * NP, h = 4 * NP, e = 5 * NP, cp = 6 * NP, tb = 7 * NP;
+    static constexpr int w = 0, C = NP, g = 2 * NP, gi = 3 * NP, h = 4 * NP, tb = 5 * NP;
 };
 
 __host__ __device__ inline int table_doubles(const MechDev &M) {
@@ -103,8 +108,7 @@ __host__ __device__ inline int table_doubles(const MechDev &M) {
 constexpr int kLockDoubles = 8;   // slot locks (up to 16 ints) ahead of the slots
 
 // The Jacobian slot of one wavefront.  With as many slots as wavefronts
-// (nslots == 0 here: a private slot) nothing is shared and the Jacobian stays
-// valid until the next assembly; otherwise a slot is taken from the pool with
+// (nslots == 0 here: a private slot) nothing is shared; otherwise a slot is taken from the pool with
 // an LDS compare-and-swap before assembly and given back once the iteration
 // matrix is in registers.  A holder never waits for anything, so every
 // waiting wavefront eventually gets a slot.
@@ -150,8 +154,9 @@ struct JacSlot {
 };
 
 // -----------------------------------------------------------------------------
-// f(y), and with JAC the analytic Jacobian into LDS (row-major, stride ldj).
-// Returns f_r on lane r.  All lanes of the wave must call it.
+// f(y), f_r on lane r; with RHS_MATRIX also lane r's row of the iteration
+// matrix diag I - J in registers, with RHS_JAC the Jacobian itself in the slot
+// Jl (row-major, stride ldj).  All lanes of the wave must call it.
 // -----------------------------------------------------------------------------
 // Species sums: with at most 16 unknowns every species sits in lanes 0..15.
 template <int NP>
@@ -160,10 +165,24 @@ __device__ __forceinline__ double species_sum(double v) {
     else return wave_sum(v);
 }
 
-template <int NP, bool JAC, bool LT, bool FO>
+// The padded matrix sizes; a mechanism of n unknowns takes the smallest NP >= n,
+// so n is above the size before it.
+#define CHEM_NP_LIST(X) X(12) X(16) X(24) X(32) X(40) X(48) X(54) X(56) X(64)
+__host__ __device__ constexpr int below_np(int np) {
+    int b = 0;
+#define BELOW(v) if (v < np) b = v;
+    CHEM_NP_LIST(BELOW)
+#undef BELOW
+    return b;
+}
+
+enum { RHS_F = 0, RHS_MATRIX = 1, RHS_JAC = 2 };
+
+template <int NP, int MODE, bool LT, bool FO>
 __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const double p,
                                            const double y, double *__restrict__ lds,
-                                           double *__restrict__ Jl) {
+                                           double *__restrict__ Jl, const double diag, double (&mat)[NP]) {
+    constexpr bool JAC = MODE != RHS_F;
     // The memory clobber keeps the descriptor loads, and the opaque lane index
     // every per-lane address, local to this call instead of being hoisted out
     // of the step loop and held in registers across it.  The sizes are made
@@ -181,8 +200,6 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     double *__restrict__ gl = lds + SM::g;
     double *__restrict__ gil = lds + SM::gi;
     double *__restrict__ hl = lds + SM::h;
-    double *__restrict__ el = lds + SM::e;
-    double *__restrict__ cpl = lds + SM::cp;
     double *__restrict__ tbl = lds + SM::tb;
 
     const double T = readlane_d(y, 0);
@@ -233,11 +250,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         const double gx = gRT - ln_patm_RT;
         gl[k] = exp_d(gx);
         gil[k] = exp_d(-gx);
-        if (JAC) {
-            hl[k] = hRT;
-            el[k] = hRT * invWk;
-            cpl[k] = cpR * invWk;
-        }
+        if (JAC) hl[k] = hRT;
     }
     if (lane <= N) wl[lane] = 0.0;
     if (JAC) {
@@ -368,11 +381,19 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         const double cpf = species_sum<NP>(sp ? cpR * invWk * fk : 0.0);
         const double dcps = species_sum<NP>(sp ? y * dcpR * invWk : 0.0);
         const double Wbar = recip_nr(sumYW);
-        // species rows: chain rule from concentrations to (T, Y)
-        if (sp) {
-            double *row = Jl + lane * ldj;
-            const double tbk = tbl[lane];
-            double s0 = 0.0, s1 = 0.0;
+        // Chain rule from concentrations to (T, Y).  The slot holds the raw
+        // sums x_kc = d omega_k / d C_c (column 0: d omega_k / dT); with
+        // s_k = sum_l (x_kl + tb_k) C_l,
+        //   J_kc = (W_k x_kc + g_k) / W_c,  g_k = W_k tb_k + f_k Wbar - W_k Wbar s_k / rho,
+        //   J_k0 = W_k (x_k0 - s_k / T) / rho + f_k / T,
+        //   sum_k e_k J_kc = (sum_k H_k x_kc + sum_k e_k g_k) / W_c,  e_k = H_k / W_k,
+        // so the rows stay raw in LDS, and the map is applied where they are
+        // read into the matrix.  (Mapping them in LDS first cost two more
+        // passes over the slot: this part went from 12 to 7 % of an attempt.)
+        double *row = Jl + (lane < n ? lane : 0) * ldj;
+        double s0 = 0.0, s1 = 0.0;
+        {
+            const double tbk = tbl[lane < n ? lane : 0];
             int l = 0;
 #pragma unroll 4
             for (; l + 1 < N; l += 2) {
@@ -380,36 +401,61 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
                 s1 += (row[2 + l] + tbk) * Cl[l + 1];
             }
             if (l < N) s0 += (row[1 + l] + tbk) * Cl[l];
-            const double s = s0 + s1;
-            const double cst = fk * Wbar - Wk * Wbar * s * irho;
-            if (LT) {
-                // 1/W_i from the species records in the shared table (broadcast reads)
-#pragma unroll 8
-                for (int i = 0; i < N; ++i)
-                    row[1 + i] = lds_all[2 * (7 * N + i) + 1] * (Wk * (row[1 + i] + tbk) + cst);
-            } else {
-                const auto *iw = gbl(M.invW);
-#pragma unroll 8
-                for (int i = 0; i < N; ++i) row[1 + i] = iw[i] * (Wk * (row[1 + i] + tbk) + cst);
-            }
-            row[0] = Wk * irho * (row[0] - s * invT) + fk * invT;
         }
-        wave_sync();
-        // temperature row: J_T,c = -(sum_k e_k J_kc)/cp - f_T dcp/dy_c / cp
-        if (lane < n) {
-            double a0 = 0.0, a1 = 0.0;
+        const double s = s0 + s1;
+        const double ek = sp ? hRT * invWk : 0.0;
+        const double gk = sp ? Wk * tbl[lane] + (fk * Wbar - Wk * Wbar * s * irho) : 0.0;
+        const double Jk0 = sp ? Wk * irho * (row[0] - s * invT) + fk * invT : 0.0;
+        const double eg = species_sum<NP>(ek * gk);
+        const double eJ0 = species_sum<NP>(ek * Jk0);
+        // temperature row, lane = column
+        double h0 = 0.0, h1 = 0.0;
+        {
+            const double *col = Jl + (lane < n ? lane : 0);
             int kk = 0;
 #pragma unroll 4
             for (; kk + 1 < N; kk += 2) {
-                a0 += el[kk] * Jl[(kk + 1) * ldj + lane];
-                a1 += el[kk + 1] * Jl[(kk + 2) * ldj + lane];
+                h0 += hl[kk] * col[(kk + 1) * ldj];
+                h1 += hl[kk + 1] * col[(kk + 2) * ldj];
             }
-            if (kk < N) a0 += el[kk] * Jl[(kk + 1) * ldj + lane];
-            const double acc = (a0 + a1) * T;
-            double v;
-            if (lane == 0) v = -(cpf + acc) * icps - fT * dcps * icps;
-            else v = -acc * icps - fT * cpl[lane - 1] * icps;
-            Jl[lane] = v;
+            if (kk < N) h0 += hl[kk] * col[(kk + 1) * ldj];
+        }
+        // times W_c, undone when the row is read like the others
+        const double vT = lane == 0 ? -(cpf + eJ0 * T) * icps - fT * dcps * icps
+                                    : -((h0 + h1) + eg) * T * icps - fT * cpR * icps;
+        wave_sync();
+        if (lane < n) {
+            Jl[lane] = vT;
+            if (MODE == RHS_MATRIX) {
+                // the diagonal is shifted in place: W_k / W_k = 1
+                if (lane == 0) row[0] = vT - diag;
+                else { row[0] = Jk0; row[lane] -= diag; }
+            } else if (lane > 0) {
+                row[0] = Jk0;
+            }
+        }
+        wave_sync();
+        const double wr = lane == 0 ? 1.0 : Wk;   // row 0 holds its values as they are
+        if (MODE == RHS_MATRIX) {
+            // rows past the matrix are those of the identity; columns past it
+            // exist only where n may be below NP
+            const bool live = lane < n;
+            const double nw = live ? -wr : 0.0, ng = -gk;
+            mat[0] = live ? -row[0] : 0.0;
+#pragma unroll
+            for (int c = 1; c < NP; ++c) {
+                if (c <= below_np(NP) || c < n) {
+                    const double iw = LT ? lds_all[2 * (7 * N + c - 1) + 1] : (double)gbl(M.invW)[c - 1];
+                    mat[c] = iw * fma(nw, row[c], ng);
+                } else {
+                    mat[c] = lane == c ? 1.0 : 0.0;
+                }
+            }
+        } else if (lane < n) {
+            for (int c = 1; c < n; ++c) {
+                const double iw = LT ? lds_all[2 * (7 * N + c - 1) + 1] : (double)gbl(M.invW)[c - 1];
+                row[c] = iw * fma(wr, row[c], gk);
+            }
         }
         wave_sync();
     }
@@ -558,55 +604,16 @@ __device__ __forceinline__ double gj_solve(const double (&a)[NP], const double d
     return lane_id() < NP ? b * dinv : 0.0;
 }
 
-template <int NP>
-__device__ __forceinline__ void build_matrix(const MechDev *__restrict__ Mp,
-                                             double *__restrict__ J, double diag,
-                                             double (&a)[NP]) {
-    asm volatile("" ::: "memory");
-    const MechDev &M = *Mp;
-    int lane = lane_id();
-    asm volatile("" : "+v"(lane));
-    // n is made opaque here so that the per-column tests of the general case
-    // are formed at each build: hoisted out of the step loop they held some
-    // 160 scalar registers, spilled to vector lanes and read back each attempt
-    int n = M.n;
-    asm volatile("" : "+s"(n));
-    const bool row_ok = lane < n;
-    double *Jl = J + (row_ok ? lane : 0) * M.ldj;
-    if (n == NP) {
-        // every row and column is the mechanism's.  The diagonal is shifted in
-        // place (x - diag, then negated, rounds as diag - x) and put back
-        // after the reads, so the columns need no per-lane test; rows past
-        // the matrix get zeros.
-        double d = 0.0;
-        if (row_ok) {
-            d = Jl[lane];
-            Jl[lane] = d - diag;
-        }
-        const double sc = row_ok ? -1.0 : 0.0;
-#pragma unroll
-        for (int c = 0; c < NP; ++c) a[c] = Jl[c] * sc;
-        if (row_ok) Jl[lane] = d;
-        return;
-    }
-#pragma unroll
-    for (int c = 0; c < NP; ++c) {
-        const double x = Jl[c < n ? c : 0];
-        double v = (row_ok && c < n) ? -x : 0.0;
-        if (c == lane) v += row_ok ? diag : 1.0;
-        a[c] = v;
-    }
-}
-
-// One Rodas4 attempt of size h from y (f0 = f(y), J in the wavefront's slot,
-// which is given back once the iteration matrix is built).  Returns false
-// when M is singular.  ynew and err are per lane.
+// One Rodas4 attempt of size h from y.  The Jacobian slot is held from the
+// assembly of f0 = f(y) and J until the iteration matrix is in registers.
+// Returns false when M is singular.  ynew and err are per lane.
 template <int NP, bool LT, bool FO>
 __device__ __forceinline__ bool rodas_attempt(const MechDev *__restrict__ M, double p, double y,
-                                              double f0, double h, double *lds, JacSlot &js,
-                                              double &ynew, double &err) {
+                                              double h, double *lds, JacSlot &js, double &ynew,
+                                              double &err) {
     double a[NP];
-    build_matrix<NP>(M, js.J, 1.0 / (kGamma * h), a);
+    js.acquire();
+    const double f0 = rhs_eval<NP, RHS_MATRIX, LT, FO>(M, p, y, lds, js.J, 1.0 / (kGamma * h), a);
     js.release();
     int pk;
     double dinv;
@@ -631,7 +638,7 @@ __device__ __forceinline__ bool rodas_attempt(const MechDev *__restrict__ M, dou
                 default: STAGE_Y(5, 0) STAGE_Y(5, 1) STAGE_Y(5, 2) STAGE_Y(5, 3) STAGE_Y(5, 4) break;
 #undef STAGE_Y
             }
-            rv = rhs_eval<NP, false, LT, FO>(M, p, ys, lds, nullptr);
+            rv = rhs_eval<NP, RHS_F, LT, FO>(M, p, ys, lds, nullptr, 0.0, a);
             double cu = 0.0;
             switch (s) {
 #define STAGE_C(i, j) cu = fma(kRodasC[i][j], u##j, cu);
@@ -747,24 +754,13 @@ __device__ __forceinline__ void integrate_cell(const MechDev *__restrict__ M, co
     double hnext = h, t = 0.0;
     int nacc = 0, nrej = 0, status = 0;
     bool rej_last = false;
-    // jac: the Jacobian of y is in the slot (a pooled slot is given back
-    // after each matrix build, so a rejected step assembles it again; the
-    // same y gives the same bits)
-    js.acquire();
-    double f0 = rhs_eval<NP, true, LT, FO>(M, p, y, lds, js.J);
-    bool jac = true;
     while (t < dt) {
         if (nacc + nrej >= P.max_steps) { status = 1; break; }
         bool last = false;
         if (h >= dt - t) { h = dt - t; last = true; }
         if (h < P.hmin_frac * dt) { status = 2; break; }
-        if (!jac) {
-            js.acquire();
-            f0 = rhs_eval<NP, true, LT, FO>(M, p, y, lds, js.J);
-        }
         double ynew = 0.0, ev = 0.0;
-        const bool ok = rodas_attempt<NP, LT, FO>(M, p, y, f0, h, lds, js, ynew, ev);
-        jac = !js.pooled();
+        const bool ok = rodas_attempt<NP, LT, FO>(M, p, y, h, lds, js, ynew, ev);
         double e = 0.0;
         bool bad = !ok;
         if (ok) {
@@ -783,11 +779,6 @@ __device__ __forceinline__ void integrate_cell(const MechDev *__restrict__ M, co
             hnext = uniform_d(h * fac);
             h = hnext;
             rej_last = false;
-            if (t < dt) {
-                js.acquire();
-                f0 = rhs_eval<NP, true, LT, FO>(M, p, y, lds, js.J);
-                jac = true;
-            }
         } else {
             const double fac = bad ? 0.2 : fmax(0.2, 0.9 * rsqrt(sqrt(e)));
             h = uniform_d(h * fac);
@@ -795,7 +786,6 @@ __device__ __forceinline__ void integrate_cell(const MechDev *__restrict__ M, co
             rej_last = true;
         }
     }
-    js.release();
     if (status == 0 && wave_any(lane < n && !isfinite(y))) status = 3;
     if (lane == 0) P.T[cell] = y;
     else if (lane <= N) P.Y[(int64_t)(lane - 1) * P.ncells + cell] = y;
@@ -884,22 +874,35 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_integrate_queue(const Mech
     }
 }
 
-// f(y) and J(y) per cell (kernel-level parity check of the rate/Jacobian code)
+// f(y) and J(y) per cell, in persistent workgroups whose wavefronts, each with a
+// private Jacobian slot, share the record table and take the cells in turn.
+// Bound by the assembly's chain with one wavefront per SIMD (the slots fill the
+// LDS); copying the 27 KB table for every cell had cost as much again.  The
+// rows leave LDS as they lie, n consecutive doubles an instruction.
 template <int NP>
-__global__ __launch_bounds__(64) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
-                                                     double *fout, double *Jout) {
+__global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
+                                                                   double *fout, double *Jout) {
     JacSlot js;
     double *lds = init_lds<NP, true>(M, 0, js);
-    const int64_t cell = blockIdx.x;
-    const int lane = lane_id(), n = M->n, N = M->N;
-    double y = 0.0;
-    if (lane == 0) y = P.T[cell];
-    else if (lane <= N) y = P.Y[(int64_t)(lane - 1) * P.ncells + cell];
-    const double f = rhs_eval<NP, true, true, true>(M, P.p[cell], y, lds, js.J);
-    if (fout && lane < n) fout[cell * n + lane] = f;
-    if (Jout)
-        for (int i = lane; i < n * n; i += 64)
-            Jout[cell * n * n + i] = js.J[(i / n) * M->ldj + (i % n)];
+    const int lane = lane_id(), n = M->n, N = M->N, ldj = M->ldj;
+    const int wpb = (int)(blockDim.x >> 6);
+    for (int64_t cell = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); cell < P.ncells;
+         cell += (int64_t)gridDim.x * wpb) {
+        double y = 0.0;
+        if (lane == 0) y = P.T[cell];
+        else if (lane <= N) y = P.Y[(int64_t)(lane - 1) * P.ncells + cell];
+        double a[NP];   // not used
+        const double f = rhs_eval<NP, RHS_JAC, true, true>(M, P.p[cell], y, lds, js.J, 0.0, a);
+        if (lane < n) {
+            if (fout) fout[cell * n + lane] = f;
+            if (Jout) {
+                double *out = Jout + cell * n * n + lane;
+#pragma unroll 8
+                for (int r = 0; r < n; ++r) out[r * n] = js.J[r * ldj + lane];
+            }
+        }
+        wave_sync();
+    }
 }
 
 template <int NP>
@@ -913,9 +916,8 @@ __global__ __launch_bounds__(64) void k_rodas_step(const MechDev *__restrict__ M
     if (lane == 0) y = P.T[cell];
     else if (lane <= N) y = P.Y[(int64_t)(lane - 1) * P.ncells + cell];
     const double p = P.p[cell];
-    const double f0 = rhs_eval<NP, true, true, true>(M, p, y, lds, js.J);
     double ynew = 0.0, err = 0.0;
-    const bool ok = rodas_attempt<NP, true, true>(M, p, y, f0, h, lds, js, ynew, err);
+    const bool ok = rodas_attempt<NP, true, true>(M, p, y, h, lds, js, ynew, err);
     if (!ok) { ynew = NAN; err = NAN; }
     if (lane < n) {
         ynew_out[cell * n + lane] = ynew;
@@ -924,9 +926,8 @@ __global__ __launch_bounds__(64) void k_rodas_step(const MechDev *__restrict__ M
 }
 
 // -----------------------------------------------------------------------------
-// host-side launchers, one instantiation per padded size
+// host-side launchers, one instantiation per padded size (CHEM_NP_LIST, above)
 // -----------------------------------------------------------------------------
-#define CHEM_NP_LIST(X) X(12) X(16) X(24) X(32) X(40) X(48) X(54) X(56) X(64)
 
 // The host side is built as two translation units that compile in parallel:
 // part 0 (this file) instantiates the kernels for mechanisms with plain
@@ -1055,13 +1056,24 @@ hipError_t launch_integrate_fo(int NP, const MechDev &M, const MechDev *Md, cons
 
 hipError_t launch_eval_rhs_jac(int NP, const MechDev &M, const MechDev *Md, const IntParams &P,
                                double *f, double *J, hipStream_t s) {
-    const size_t sh = lds_bytes(M, WaveLayout{1, 1});
+    // as many wavefronts as have room for a slot each, one workgroup per CU
+    int w = max_wpb(NP);
+    while (w > 1 && lds_bytes(M, WaveLayout{w, w}) > kLdsCap) --w;
+    const size_t sh = lds_bytes(M, WaveLayout{w, w});
+    int dev = 0, cus = 0;
+    hipError_t e;
+    if ((e = hipGetDevice(&dev)) ||
+        (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))
+        return e;
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(kLdsCap / sh, (size_t)(8 / w)));
+    const int64_t need = (P.ncells + w - 1) / w;
+    const unsigned grid = (unsigned)std::min<int64_t>(need, (int64_t)cus * per_cu);
     switch (NP) {
 #define CASE(v)                                                                                 \
     case v:                                                                                     \
         hipFuncSetAttribute((const void *)k_eval_rhs_jac<v>,                                    \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);               \
-        hipLaunchKernelGGL(k_eval_rhs_jac<v>, dim3((unsigned)P.ncells), dim3(64), sh, s, Md, P, f, J); \
+        hipLaunchKernelGGL(k_eval_rhs_jac<v>, dim3(grid), dim3(64 * w), sh, s, Md, P, f, J);    \
         return hipGetLastError();
         CHEM_NP_LIST(CASE)
 #undef CASE
