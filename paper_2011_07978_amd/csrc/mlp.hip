@@ -16,6 +16,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 #include <random>
 #include <vector>
@@ -43,93 +44,87 @@ __device__ __forceinline__ float gelu_df(float z) {
            z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// ------------------------------------------------------------------ GEMM ----
-// C[m][n] = sum_k A[m][k] B[n][k]  (A: M x K, B: N x K, bf16, k contiguous).
-// Workgroup tile 64 x 64, four waves of 32 x 32, each 2 x 2 MFMA 16x16x32 blocks.
-// MFMA operand layout (gfx950, checked on hardware): lane l holds A row l%16,
-// k = 8(l/16)..+7; B column l%16, same k; D rows 4(l/16)+i, column l%16.
-enum { EPI_HID = 0, EPI_OUT = 1, EPI_PLAIN = 2, EPI_OUT_T = 3 };
-struct GemmEpi {
-    const float *bias;
-    uint16_t *H; int ldh;      // bf16 GELU output
-    uint16_t *HT; int ldht;    // bf16 GELU output, transposed (nullable)
-    float *Z; int ldz;         // f32 pre-activation (nullable)
-    float *C; int ldc;         // f32 output
-};
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
 
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_nt(const uint16_t *__restrict__ A, int lda,
-                                                 const uint16_t *__restrict__ B, int ldb, int M,
-                                                 int N, int K, GemmEpi e) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int m0 = blockIdx.x * 64 + (w >> 1) * 32, n0 = blockIdx.y * 64 + (w & 1) * 32;
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    // split-K launches (gridDim.z > 1): slice z covers k in [zK, (z+1)K) and
-    // writes its partial product to its own M x ldc slab of C
-    A += (size_t)blockIdx.z * K;
-    B += (size_t)blockIdx.z * K;
-    f32x4 acc[2][2];
+// GELU of four values as bfloat16, the bits of f2bf(gelu_f(z)).  The network
+// spends more vector time here than matrix time (about 46 instructions a value
+// with the library's erf, which takes both of its branches in most
+// wavefronts), so a value is first formed as max(z, 0) - |z| Q(|z|), Q(t) =
+// erfc(t / sqrt 2) / 2 = 2^P(t) with P the minimax polynomial of degree 7 on
+// [0, 5.5] (Q within 1.1e-7).  That and gelu_f are within 3e-7 |z| of each
+// other; where both ends of that interval round to the same bfloat16 the
+// result is known, and only where they do not (some 0.1 % of the values, and
+// z < -4) is it computed the long way.  Checked for all 2^32 floats.
+__device__ __forceinline__ uint2 gelu_bf16x4(f32x4 z) {
+    uint32_t w[4], bad = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero8 = {};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        bf16x8 a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int row = m0 + 16 * i + r16;
-            a[i] = row < M ? *(const bf16x8 *)(A + (size_t)row * lda + k0 + kq) : zero8;
-            const int col = n0 + 16 * i + r16;
-            b[i] = col < N ? *(const bf16x8 *)(B + (size_t)col * ldb + k0 + kq) : zero8;
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int r = 0; r < 4; ++r) {
+        const float a = fabsf(z[r]), t = fminf(a, 5.5f);
+        float P = fmaf(t, 8.47015417e-06f, -5.39036701e-05f);
+        P = fmaf(t, P, -0.000421235978f);
+        P = fmaf(t, P, 0.0073892721f);
+        P = fmaf(t, P, -0.0526911095f);
+        P = fmaf(t, P, -0.459153146f);
+        P = fmaf(t, P, -1.15111089f);
+        P = fmaf(t, P, -0.999999881f);
+        const float g = fmaf(-a, __builtin_amdgcn_exp2f(P), fmaxf(z[r], 0.0f));
+        const float d = fmaf(3e-7f, a, 1e-37f);   // and subnormal results
+        w[r] = pk_bf16(g - d, g + d);
+        bad |= w[r] ^ (w[r] >> 16);
     }
+    if (__builtin_amdgcn_ballot_w64((bad & 0xffffu) != 0)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + 16 * i + 4 * (lane >> 4) + r;
-                const int col = n0 + 16 * j + r16;
-                if (row >= M || col >= N) continue;
-                const float v = acc[i][j][r];
-                if (EPI == EPI_HID) {
-                    const float z = v + e.bias[col];
-                    const uint16_t g = f2bf(gelu_f(z));
-                    e.H[(size_t)row * e.ldh + col] = g;
-                    if (e.HT) e.HT[(size_t)col * e.ldht + row] = g;
-                    if (e.Z) e.Z[(size_t)row * e.ldz + col] = z;
-                } else if (EPI == EPI_OUT) {
-                    e.C[(size_t)row * e.ldc + col] = v + e.bias[col];
-                } else if (EPI == EPI_OUT_T) {
-                    e.C[(size_t)col * e.ldc + row] = v + e.bias[col];
-                } else {
-                    e.C[((size_t)blockIdx.z * M + row) * e.ldc + col] = v;
-                }
-            }
+        for (int r = 0; r < 4; ++r) w[r] = f2bf(gelu_f(z[r]));
+    }
+    return {(w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
 }
 
-template <int EPI>
-static void gemm(const uint16_t *A, int lda, const uint16_t *B, int ldb, int M, int N, int K,
-                 const GemmEpi &e, hipStream_t s) {
-    dim3 grid((M + 63) / 64, (N + 63) / 64);
-    hipLaunchKernelGGL(k_gemm_nt<EPI>, grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, e);
-}
-
-// dst[i] = sum over z of part[z][i], slices added in order
-__global__ __launch_bounds__(256) void k_sum_slices(const float *part, int S, int64_t n, float *dst) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.0f;
-    for (int z = 0; z < S; ++z) s += part[(size_t)z * n + i];
-    dst[i] = s;
-}
+// ------------------------------------------------------------ tile layers ----
+// One layer for a tile of 16 RB rows in one workgroup of four wavefronts: a
+// wavefront takes NBK blocks of 16 output columns from n0, with 16x16x32 MFMA
+// blocks accumulating over k in order.  Operands (gfx950, checked on hardware):
+// lane l holds A row l%16, k = 8(l/16)..+7; B column l%16, same k; D rows
+// 4(l/16)+i, column l%16.  The weights are the A operand, so a lane's four
+// results are four neighbouring columns of one batch row and leave in one
+// store.  The weights of a layer (K x 16 NBK per wavefront) are loaded in one
+// go, ahead of the previous layer's activation function, which covers their
+// way from L2.
+template <int K, int NBK>
+struct WTile {
+    bf16x8 w[K / 32][NBK];
+    __device__ __forceinline__ void load(const uint16_t *__restrict__ W, int n0) {
+        const int lane = threadIdx.x & 63;
+        const uint16_t *q = W + (size_t)(n0 + (lane & 15)) * K + (lane >> 4) * 8;
+#pragma unroll
+        for (int ks = 0; ks < K / 32; ++ks)
+#pragma unroll
+            for (int j = 0; j < NBK; ++j) w[ks][j] = *(const bf16x8 *)(q + (size_t)16 * j * K + 32 * ks);
+    }
+    template <int RB>
+    __device__ __forceinline__ void apply(const uint16_t *In, int ldi, f32x4 (&acc)[RB][NBK]) const {
+        const int lane = threadIdx.x & 63;
+        const uint16_t *q = In + (lane & 15) * ldi + (lane >> 4) * 8;
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NBK; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < K / 32; ++ks) {
+            bf16x8 b[RB];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) b[i] = *(const bf16x8 *)(q + 16 * i * ldi + 32 * ks);
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < NBK; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][j], b[i], acc[i][j], 0, 0, 0);
+        }
+    }
+};
 
 // ------------------------------------------------------------- features ----
 __device__ __forceinline__ double raw_feature(const FeatSrc &f, int64_t i, int c) {
@@ -140,35 +135,6 @@ __device__ __forceinline__ double raw_feature(const FeatSrc &f, int64_t i, int c
     return 0.0;
 }
 
-// per-feature sum, sum of squares, min, max (FP64), one block per feature
-__global__ __launch_bounds__(256) void k_feature_moments(FeatSrc f, int ncol, double *out) {
-    const int c = blockIdx.x;
-    double s = 0.0, s2 = 0.0, mn = INFINITY, mx = -INFINITY;
-    for (int64_t i = threadIdx.x; i < f.n; i += blockDim.x) {
-        const double v = raw_feature(f, i, c);
-        s += v;
-        s2 += v * v;
-        mn = fmin(mn, v);
-        mx = fmax(mx, v);
-    }
-    __shared__ double sh[4][256];
-    sh[0][threadIdx.x] = s; sh[1][threadIdx.x] = s2; sh[2][threadIdx.x] = mn; sh[3][threadIdx.x] = mx;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) {
-            sh[0][threadIdx.x] += sh[0][threadIdx.x + st];
-            sh[1][threadIdx.x] += sh[1][threadIdx.x + st];
-            sh[2][threadIdx.x] = fmin(sh[2][threadIdx.x], sh[2][threadIdx.x + st]);
-            sh[3][threadIdx.x] = fmax(sh[3][threadIdx.x], sh[3][threadIdx.x + st]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[4 * c] = sh[0][0]; out[4 * c + 1] = sh[1][0];
-        out[4 * c + 2] = sh[2][0]; out[4 * c + 3] = sh[3][0];
-    }
-}
-
 // targets: the increments dY_k = Y1_k - Y0_k (k < N) and dT = T1 - T0
 // Increments in the network's output scale: asinh(dY_k / S_Y), asinh(dT / S_T).
 constexpr double S_Y = 1e-12, S_T = 1e-6;
@@ -176,77 +142,84 @@ __device__ __forceinline__ double raw_target(const TgtSrc &t, int64_t i, int c) 
     if (c < t.N) return asinh((t.Y1[(int64_t)c * t.n + i] - t.Y0[(int64_t)c * t.n + i]) / S_Y);
     return asinh((t.T1[i] - t.T0[i]) / S_T);
 }
-__global__ __launch_bounds__(256) void k_target_moments(TgtSrc t, double *out) {
-    const int c = blockIdx.x;
-    double s = 0.0, s2 = 0.0;
-    for (int64_t i = threadIdx.x; i < t.n; i += blockDim.x) {
-        const double v = raw_target(t, i, c);
-        s += v;
-        s2 += v * v;
+
+// Per column sum and sum of squares (FP64), for the nfeat features also min and
+// max, one block per column: column c < nfeat is a feature (4 results from
+// out + 4 c), the others targets (2 each from out + 4 nfeat).  The values take
+// longest (asinh, log: some 200 vector instructions), so 1024 threads form them,
+// and 256 add them up in LDS in the order i = t, t + 256, ... .
+// 65,536 samples, 110 columns: see the figures at train.
+constexpr int MOM_T = 1024;
+__global__ __launch_bounds__(MOM_T) void k_moments(FeatSrc f, TgtSrc t, int nfeat, double *out) {
+    const int c = blockIdx.x, tid = threadIdx.x;
+    __shared__ double val[2][MOM_T];
+    __shared__ double sh[4][256];
+    double s = 0.0, s2 = 0.0, mn = INFINITY, mx = -INFINITY;
+    int buf = 0;
+    for (int64_t base = 0; base < f.n; base += MOM_T, buf ^= 1) {
+        const int64_t i = base + tid;
+        if (i < f.n) val[buf][tid] = c < nfeat ? raw_feature(f, i, c) : raw_target(t, i, c - nfeat);
+        __syncthreads();
+        if (tid < 256) {
+#pragma unroll
+            for (int q = 0; q < MOM_T / 256; ++q) {
+                if (base + 256 * q + tid >= f.n) break;
+                const double v = val[buf][256 * q + tid];
+                s += v;
+                s2 += v * v;
+                mn = fmin(mn, v);
+                mx = fmax(mx, v);
+            }
+        }
     }
-    __shared__ double sh[2][256];
-    sh[0][threadIdx.x] = s; sh[1][threadIdx.x] = s2;
+    if (tid < 256) { sh[0][tid] = s; sh[1][tid] = s2; sh[2][tid] = mn; sh[3][tid] = mx; }
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) {
-            sh[0][threadIdx.x] += sh[0][threadIdx.x + st];
-            sh[1][threadIdx.x] += sh[1][threadIdx.x + st];
+        if (tid < st) {
+            sh[0][tid] += sh[0][tid + st];
+            sh[1][tid] += sh[1][tid + st];
+            sh[2][tid] = fmin(sh[2][tid], sh[2][tid + st]);
+            sh[3][tid] = fmax(sh[3][tid], sh[3][tid + st]);
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) { out[2 * c] = sh[0][0]; out[2 * c + 1] = sh[1][0]; }
+    if (tid == 0) {
+        double *o = c < nfeat ? out + 4 * c : out + 4 * nfeat + 2 * (c - nfeat);
+        o[0] = sh[0][0];
+        o[1] = sh[1][0];
+        if (c < nfeat) { o[2] = sh[2][0]; o[3] = sh[3][0]; }
+    }
 }
 
-// rows r < B of the batch from samples idx[r] (nullable: base + r):
-// X[r][c] bf16 normalised features, XT[c][r] its transpose (nullable),
-// Tg[r][c] normalised targets (nullable)
-__global__ __launch_bounds__(256) void k_build_rows(FeatSrc f, TgtSrc t, const int *idx, int64_t base,
-                                                    int B, const float *norm, uint16_t *X,
-                                                    uint16_t *XT, int ldxt, float *Tg) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int c = threadIdx.x & 63;
-    if (r >= B) return;
-    const int64_t i = idx ? (int64_t)idx[r] : base + r;
+// Rows r < B from samples idx[r] (nullable: r): X[r][c] bf16 normalised
+// features and Tg[r][c] normalised targets.  A block takes 64 rows, lane = row,
+// so that neighbouring samples of a feature are one read, and turns them in LDS.
+__global__ __launch_bounds__(256) void k_build_rows(FeatSrc f, TgtSrc t, const int *idx, int64_t B,
+                                                    const float *norm, uint16_t *X, float *Tg) {
+    __shared__ uint16_t xs[64][S_IN + 2];
+    __shared__ float ts[64][S_OUT + 1];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    const int rows = B - r0 < 64 ? (int)(B - r0) : 64;
     const int nfeat = f.N + 3;
-    uint16_t v = 0;
-    if (c < nfeat) v = f2bf((float)((raw_feature(f, i, c) - norm[c]) / norm[64 + c]));
-    X[(size_t)r * S_IN + c] = v;
-    if (XT) XT[(size_t)c * ldxt + r] = v;
-    if (Tg) {
+    const int64_t r = r0 + (lane < rows ? lane : 0);
+    const int64_t i = idx ? (int64_t)idx[r] : r;
+    for (int c = w; c < S_IN; c += 4) {
+        uint16_t v = 0;
+        if (c < nfeat) v = f2bf((float)((raw_feature(f, i, c) - norm[c]) / norm[64 + c]));
+        xs[lane][c] = v;
         float tv = 0.0f;
         if (c < t.N + 1) tv = (float)((raw_target(t, i, c) - norm[128 + c]) / norm[192 + c]);
-        Tg[(size_t)r * S_OUT + c] = tv;
+        ts[lane][c] = tv;
+    }
+    __syncthreads();
+    for (int q = w; q < rows; q += 4) {
+        X[(r0 + q) * S_IN + lane] = xs[q][lane];
+        Tg[(r0 + q) * S_OUT + lane] = ts[q][lane];
     }
 }
 
 // ------------------------------------------------------------- backward ----
-// dO = 2 (out - target) / (B * nout) for the first nout columns, 0 elsewhere
-__global__ __launch_bounds__(256) void k_out_grad(const float *out, const float *Tg, int B, int nout,
-                                                  float *dOf, uint16_t *dZ, uint16_t *dZT, int ldt,
-                                                  double *loss_part) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int c = threadIdx.x & 63;
-    float g = 0.0f;
-    double l2 = 0.0;
-    if (r < B && c < nout) {
-        const float e = out[(size_t)r * S_OUT + c] - Tg[(size_t)r * S_OUT + c];
-        g = 2.0f * e / ((float)B * (float)nout);
-        l2 = (double)e * e;
-    }
-    if (r < B) {
-        dOf[(size_t)r * S_OUT + c] = g;
-        const uint16_t gb = f2bf(g);
-        dZ[(size_t)r * S_OUT + c] = gb;
-        dZT[(size_t)c * ldt + r] = gb;
-    }
-    // squared errors of the block's rows, added to the block's own running sum
-    for (int m = 32; m > 0; m >>= 1) l2 += __shfl_xor(l2, m);
-    __shared__ double sh[4];
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = l2;
-    __syncthreads();
-    if (threadIdx.x == 0) loss_part[blockIdx.x] += (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
-
 // loss[0] = sum of the n per-block running sums (one block, fixed order)
 __global__ __launch_bounds__(256) void k_sum_loss(const double *part, int n, double *loss) {
     double s = 0.0;
@@ -261,55 +234,94 @@ __global__ __launch_bounds__(256) void k_sum_loss(const double *part, int n, dou
     if (threadIdx.x == 0) loss[0] = sh[0];
 }
 
-// Column sums of src [B x ncol] (bias gradients) in two fixed-order passes:
-// block (x, y) sums rows y, y + CS_CHUNKS, ... of 64 columns into part[y][c]
-// (four row phases per block, combined in order); then one thread per column
-// adds the CS_CHUNKS partial sums in order.
 constexpr int CS_CHUNKS = 64;
 // slices of a split-K weight gradient: at most 256 workgroups of 64 x 64
 // outputs, so S M N <= 256 * 4096
 constexpr int64_t kSplitFloats = (int64_t)256 * 4096;
-__global__ __launch_bounds__(256) void k_colsum_part(const float *src, int B, int ncol, float *part) {
+
+// Column sums of the FP32 output gradients (bias gradients), first of two
+// fixed-order passes, all layers in one launch (z; 4 is the output layer, 64
+// columns): block (x, y) sums rows y, y + CS_CHUNKS, ... of 64 columns into
+// part[z][y][c] (four row phases per block, combined in order); k_gradients
+// adds the CS_CHUNKS partial sums in order.
+struct ColSrc {
+    const float *G[5];
+};
+__global__ __launch_bounds__(256) void k_colsum_part(ColSrc src, int B, float *part) {
+    const int z = blockIdx.z, ncol = z == 4 ? S_OUT : S_HID;
     const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
+    if (blockIdx.x * 64 >= ncol) return;   // whole workgroup
+    const float *g = src.G[0];
+#pragma unroll
+    for (int q = 1; q < 5; ++q)
+        if (z == q) g = src.G[q];
     float s = 0.0f;
-    if (c < ncol)
-        for (int r = blockIdx.y + CS_CHUNKS * ph; r < B; r += 4 * CS_CHUNKS) s += src[(size_t)r * ncol + c];
-    __shared__ float sh[4][64];
-    sh[ph][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (ph == 0 && c < ncol)
-        part[(size_t)blockIdx.y * ncol + c] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) +
-                                              (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
-}
-// dZ = dH * GELU'(Z) of a hidden layer as bf16 (+ transpose) and the partial
-// column sums of the FP32 dZ (the bias gradient): block (x, y) covers 64
-// columns and visits rows in the order of k_colsum_part, so the partial sums
-// are the ones k_colsum_part would form from an FP32 copy of dZ
-__global__ __launch_bounds__(256) void k_gelu_back(const float *dH, const float *Z, int B,
-                                                   uint16_t *dZ, uint16_t *dZT, int ldt, float *part) {
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-    float s = 0.0f;
-    for (int r = blockIdx.y + CS_CHUNKS * ph; r < B; r += 4 * CS_CHUNKS) {
-        const size_t t = (size_t)r * S_HID + c;
-        const float g = dH[t] * gelu_df(Z[t]);
-        s += g;
-        const uint16_t gb = f2bf(g);
-        dZ[t] = gb;
-        dZT[(size_t)c * ldt + r] = gb;
-    }
+#pragma unroll 8
+    for (int r = blockIdx.y + CS_CHUNKS * ph; r < B; r += 4 * CS_CHUNKS) s += g[(size_t)r * ncol + c];
     __shared__ float sh[4][64];
     sh[ph][threadIdx.x & 63] = s;
     __syncthreads();
     if (ph == 0)
-        part[(size_t)blockIdx.y * S_HID + c] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) +
-                                               (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
+        part[((size_t)z * CS_CHUNKS + blockIdx.y) * S_HID + c] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) +
+                                                                 (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
 }
-__global__ __launch_bounds__(256) void k_colsum_final(const float *part, int ncol, float *dst) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= ncol) return;
-    float s = 0.0f;
-    for (int y = 0; y < CS_CHUNKS; ++y) s += part[(size_t)y * ncol + c];
-    dst[c] = s;
+
+// Weight gradients dW_l = dZ_l^T H_{l-1} of all layers in one launch: M x N is
+// a few 64 x 64 tiles and K (the batch) is long, so a layer's K range is cut
+// into S slices that fill the chip; slice z writes its partial product to slab
+// z of its part (M x N), and k_gradients adds the slabs in order.  Both operands
+// are k-contiguous (the transposes written by k_mlp_train) and go straight from
+// memory to the MFMA layout; one workgroup a tile and slice, four wavefronts of
+// 32 x 32.
+struct WgradJob {
+    const uint16_t *A, *B;
+    float *C;
+    int M, N, S, first;   // first: the job's first workgroup
+};
+struct WgradJobs {
+    WgradJob j[5];
+    int ld;               // batch: row length of the operands
+};
+__global__ __launch_bounds__(256) void k_wgrad(WgradJobs jobs) {
+    WgradJob jb = jobs.j[0];
+#pragma unroll
+    for (int q = 1; q < 5; ++q)
+        if ((int)blockIdx.x >= jobs.j[q].first) jb = jobs.j[q];
+    const int t = blockIdx.x - jb.first, tm = jb.M / 64, tn = jb.N / 64;
+    const int z = t / (tm * tn), xy = t - z * (tm * tn), x = xy / tn, y = xy - x * tn;
+    const int ld = jobs.ld, K = ld / jb.S;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int m0 = x * 64 + (w >> 1) * 32, n0 = y * 64 + (w & 1) * 32;
+    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+    const uint16_t *A = jb.A + (size_t)(m0 + r16) * ld + (size_t)z * K + kq;
+    const uint16_t *B = jb.B + (size_t)(n0 + r16) * ld + (size_t)z * K + kq;
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        bf16x8 a[2], b[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            a[i] = *(const bf16x8 *)(A + (size_t)16 * i * ld + k0);
+            b[i] = *(const bf16x8 *)(B + (size_t)16 * i * ld + k0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    float *C = jb.C + (size_t)z * jb.M * jb.N;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                C[(size_t)(m0 + 16 * i + 4 * (lane >> 4) + r) * jb.N + n0 + 16 * j + r16] = acc[i][j][r];
 }
 
 // where each layer's weights sit in the FP32 blob and their bf16 copies
@@ -319,29 +331,55 @@ struct WeightCopies {
     uint16_t *Wb[5], *WbT[5];
 };
 
-// Adam on the FP32 masters; a weight (not a bias) is also written to its
-// layer's bf16 copy Wb [no x ni] and transpose WbT [ni x no]
-__global__ __launch_bounds__(256) void k_adam(float *P, const float *G, float *m, float *v, int64_t n,
-                                              float lr, float b1, float b2, float eps, float c1,
-                                              float c2, WeightCopies wc) {
+// The gradient of parameter i: the slabs of its weight gradient, or the partial
+// column sums of its bias gradient, added in order.
+struct GradParts {
+    const float *W[5];    // slabs of dW_l
+    int S[5];
+    const float *col;     // [5][CS_CHUNKS][S_HID]
+};
+// ADAM: the step on the FP32 masters, a weight (not a bias) also written to its
+// layer's bf16 copies Wb [no x ni] and WbT [ni x no]; otherwise the gradient
+// itself to G.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_gradients(GradParts gp, WeightCopies wc, int64_t n, float *G, float *P,
+                                                   float *m, float *v, float lr, float b1, float b2,
+                                                   float eps, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const float g = G[i];
+    int l = 0;
+    int64_t off = wc.off[0];
+    int no = wc.no[0], ni = wc.ni[0], S = gp.S[0];
+    const float *part = gp.W[0];
+    uint16_t *wb = wc.Wb[0], *wbt = wc.WbT[0];
+#pragma unroll
+    for (int q = 1; q < 5; ++q)
+        if (i >= wc.off[q]) {
+            l = q; off = wc.off[q]; no = wc.no[q]; ni = wc.ni[q]; S = gp.S[q]; part = gp.W[q];
+            wb = wc.Wb[q]; wbt = wc.WbT[q];
+        }
+    const int t = (int)(i - off), mn = no * ni;
+    float g = 0.0f;
+    if (t < mn) {
+#pragma unroll 8
+        for (int z = 0; z < S; ++z) g += part[(size_t)z * mn + t];
+    } else {
+        const float *col = gp.col + (size_t)l * CS_CHUNKS * S_HID + (t - mn);
+#pragma unroll 8
+        for (int y = 0; y < CS_CHUNKS; ++y) g += col[(size_t)y * S_HID];
+    }
+    if (!ADAM) {
+        G[i] = g;
+        return;
+    }
     const float mi = b1 * m[i] + (1.0f - b1) * g;
     const float vi = b2 * v[i] + (1.0f - b2) * g * g;
     m[i] = mi;
     v[i] = vi;
     const float p = P[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     P[i] = p;
-    int64_t off = wc.off[0];
-    int no = wc.no[0], ni = wc.ni[0];
-    uint16_t *wb = wc.Wb[0], *wbt = wc.WbT[0];
-#pragma unroll
-    for (int q = 1; q < 5; ++q)
-        if (i >= wc.off[q]) { off = wc.off[q]; no = wc.no[q]; ni = wc.ni[q]; wb = wc.Wb[q]; wbt = wc.WbT[q]; }
-    const int64_t t = i - off;
-    if (t < (int64_t)no * ni) {
-        const int o = (int)(t / ni), k = (int)(t % ni);
+    if (t < mn) {
+        const int o = t / ni, k = t - o * ni;
         const uint16_t b = f2bf(p);
         wb[t] = b;
         wbt[(size_t)k * no + o] = b;
@@ -542,13 +580,13 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
     if (sel) idx[off + __popcll(b & ((1ull << lane) - 1ull))] = r;
 }
 
-// The whole network for a tile of 64 selected rows in one workgroup: the
-// input tile and the hidden activations stay in LDS (bf16), weights stream
-// from L2.  Per layer, wavefront w computes output columns [64w, 64w + 64)
-// (16 of the 64 outputs in the last layer) for all 64 rows with 16x16x32
-// MFMA blocks, accumulating over k in the same order as k_gemm_nt, so the
-// outputs equal the layer-by-layer path bit for bit.  Output row r goes to
-// outT[c][r] (r = chunk position), as the acceptance kernel reads it.
+// The whole network for a tile of 64 rows in one workgroup: the input tile and
+// the hidden activations stay in LDS (bf16), weights stream from L2.
+// Wavefront w computes output columns [64w, 64w + 64) of the hidden layers, 16
+// of the 64 outputs of the last.  SELECTED: rows idx[0 .. *cnt) of the chunk,
+// row r's outputs to outT[c][r] as the acceptance kernel reads them; otherwise
+// all m rows from base, outputs row-major.
+// 100,003 rows: see the figures at forward_rows.
 constexpr int FT = 64;             // rows per tile
 constexpr int XLD = S_IN + 8;      // LDS row strides (bf16), padded against bank conflicts
 constexpr int HLD = S_HID + 8;
@@ -557,92 +595,261 @@ struct MlpW {
     const float *b[5];
 };
 
-template <int K, int NB>
-__device__ __forceinline__ void tile_layer(const uint16_t *In, int ldi, const uint16_t *__restrict__ W,
-                                           int n0, f32x4 (&acc)[4][NB]) {
+// bf16(GELU(acc + bias)) of the wavefront's 64 columns into the tile Out
+template <int RB>
+__device__ __forceinline__ void gelu_tile(const f32x4 (&acc)[RB][4], const float *__restrict__ bias, int n0,
+                                          uint16_t *Out) {
     const int lane = threadIdx.x & 63;
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + 16 * j + 4 * (lane >> 4);
+        const f32x4 bc = *(const f32x4 *)(bias + col);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        bf16x8 a[4], b[NB];
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            b[j] = *(const bf16x8 *)(W + (size_t)(n0 + 16 * j + r16) * K + k0 + kq);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const bf16x8 *)(In + (16 * i + r16) * ldi + k0 + kq);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < RB; ++i)
+            *(uint2 *)(Out + (16 * i + (lane & 15)) * HLD + col) = gelu_bf16x4(acc[i][j] + bc);
     }
 }
 
-template <int K>
-__device__ __forceinline__ void hidden_layer(const uint16_t *In, int ldi, const uint16_t *W,
-                                             const float *bias, uint16_t *Out) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int n0 = 64 * w;
-    f32x4 acc[4][4];
-    tile_layer<K, 4>(In, ldi, W, n0, acc);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = n0 + 16 * j + (lane & 15);
-            const float bc = bias[col];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 16 * i + 4 * (lane >> 4) + r;
-                Out[row * HLD + col] = f2bf(gelu_f(acc[i][j][r] + bc));
-            }
-        }
-}
-
-__global__ __launch_bounds__(256) void k_mlp_infer(FeatSrc f, int64_t base, int m, const int *idx,
-                                                   const int *cnt, const float *norm, MlpW wt,
-                                                   float *outT) {
-    extern __shared__ uint16_t sm16[];
+template <bool SELECTED>
+__global__ __launch_bounds__(256, 2) void k_mlp_infer(FeatSrc f, int64_t base, int m, const int *idx,
+                                                      const int *cnt, const float *norm, MlpW wt,
+                                                      float *out) {
+    extern __shared__ __align__(16) uint16_t sm16[];
     uint16_t *Xs = sm16, *Ha = Xs + FT * XLD, *Hb = Ha + FT * HLD;
-    const int n_sel = *cnt;
+    const int n_sel = SELECTED ? *cnt : m;
     const int t0 = blockIdx.x * FT;
     if (t0 >= n_sel) return;                       // whole workgroup
     const int rows = n_sel - t0 < FT ? n_sel - t0 : FT;
-    const int tid = threadIdx.x, c = tid & 63;
-    const int nfeat = f.N + 3;
-    for (int rr = tid >> 6; rr < FT; rr += 4) {
-        uint16_t v = 0;
-        if (rr < rows && c < nfeat)
-            v = f2bf((float)((raw_feature(f, base + idx[t0 + rr], c) - norm[c]) / norm[64 + c]));
-        Xs[rr * XLD + c] = v;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int n0 = 64 * w;
+    WTile<S_IN, 4> w0;
+    w0.load(wt.W[0], n0);
+    {
+        // lane = row, so that each feature of a tile is one coalesced read
+        const int nfeat = f.N + 3;
+        const int64_t i = base + (SELECTED ? idx[t0 + (lane < rows ? lane : 0)] : t0 + (lane < rows ? lane : 0));
+#pragma unroll 4
+        for (int c = w; c < S_IN; c += 4) {
+            uint16_t v = 0;
+            if (lane < rows && c < nfeat) v = f2bf((float)((raw_feature(f, i, c) - norm[c]) / norm[64 + c]));
+            Xs[lane * XLD + c] = v;
+        }
     }
     __syncthreads();
-    hidden_layer<S_IN>(Xs, XLD, wt.W[0], wt.b[0], Ha);
+    f32x4 acc[4][4];
+    w0.apply<4>(Xs, XLD, acc);
+    WTile<S_HID, 4> wh;
+    wh.load(wt.W[1], n0);
+    gelu_tile<4>(acc, wt.b[0], n0, Ha);
     __syncthreads();
-    hidden_layer<S_HID>(Ha, HLD, wt.W[1], wt.b[1], Hb);
+    wh.apply<4>(Ha, HLD, acc);
+    wh.load(wt.W[2], n0);
+    gelu_tile<4>(acc, wt.b[1], n0, Hb);
     __syncthreads();
-    hidden_layer<S_HID>(Hb, HLD, wt.W[2], wt.b[2], Ha);
+    wh.apply<4>(Hb, HLD, acc);
+    wh.load(wt.W[3], n0);
+    gelu_tile<4>(acc, wt.b[2], n0, Ha);
     __syncthreads();
-    hidden_layer<S_HID>(Ha, HLD, wt.W[3], wt.b[3], Hb);
+    wh.apply<4>(Ha, HLD, acc);
+    WTile<S_HID, 1> wo;
+    wo.load(wt.W[4], 16 * w);
+    gelu_tile<4>(acc, wt.b[3], n0, Hb);
     __syncthreads();
-    const int lane = tid & 63, w = tid >> 6;
-    f32x4 acc[4][1];
-    tile_layer<S_HID, 1>(Hb, HLD, wt.W[4], 16 * w, acc);
-    const int col = 16 * w + (lane & 15);
-    const float bc = wt.b[4][col];
+    f32x4 o[4][1];
+    wo.apply<4>(Hb, HLD, o);
+    const int col = 16 * w + 4 * (lane >> 4);
+    const f32x4 bc = *(const f32x4 *)(wt.b[4] + col);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        const int row = 16 * i + (lane & 15);
+        if (row >= rows) continue;
+        const f32x4 v = o[i][0] + bc;
+        if (SELECTED) {
+            const int r = idx[t0 + row];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * i + 4 * (lane >> 4) + r;
-            if (row < rows) outT[(size_t)col * m + idx[t0 + row]] = acc[i][0][r] + bc;
+            for (int q = 0; q < 4; ++q) out[(size_t)(col + q) * m + r] = v[q];
+        } else {
+            *(f32x4 *)(out + (size_t)(t0 + row) * S_OUT + col) = v;
         }
+    }
 }
 static constexpr size_t kInferLds = sizeof(uint16_t) * (size_t)FT * (XLD + 2 * HLD);
+
+// ------------------------------------------------------- training: a tile ----
+// Forward and backward of 16 RB rows of the batch in one workgroup.  The tile's
+// activations and output gradients stay in LDS; what leaves are the transposes
+// that the weight gradients contract over the batch (X, H_l, dZ_l) and the FP32
+// output gradients whose column sums are the bias gradients.  The
+// pre-activations go through a scratch array laid out by thread (each thread
+// reads back what it wrote).  Layer by layer through memory, with a launch per
+// product and 2-byte transposed stores, this was 21 of an Adam step's 36
+// launches.
+struct TrainBufs {
+    float *Z;                              // [tile][layer][block][thread] f32x4
+    uint16_t *XT, *HT[4], *dZT[4], *dZ5T;  // [column][B]
+    float *G[4], *dOf;                     // [row][column]
+    double *lpart;                         // squared error per workgroup, running
+};
+
+// dst[c][r0 ..] = columns of a tile of 16 RB rows
+template <int RB, int NC>
+__device__ __forceinline__ void store_transposed(const uint16_t *tile, int ld, uint16_t *__restrict__ dst, int B,
+                                                 int r0) {
+#pragma unroll
+    for (int u0 = 0; u0 < NC * 2 * RB; u0 += 256) {
+        const int u = u0 + threadIdx.x;
+        if (NC * 2 * RB < 256 && u >= NC * 2 * RB) break;
+        const int c = u % NC, part = u / NC;
+        uint32_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = tile[(8 * part + 2 * q) * ld + c] | ((uint32_t)tile[(8 * part + 2 * q + 1) * ld + c] << 16);
+        *(uint4 *)(dst + (size_t)c * B + r0 + 8 * part) = uint4{v[0], v[1], v[2], v[3]};
+    }
+}
+
+// z = acc + bias kept in the scratch, bf16(GELU(z)) into the tile Out
+template <int RB>
+__device__ __forceinline__ void train_hidden(const f32x4 (&acc)[RB][4], const float *__restrict__ bias, int n0,
+                                             f32x4 *__restrict__ Z, uint16_t *Out) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + 16 * j + 4 * (lane >> 4);
+        const f32x4 bc = *(const f32x4 *)(bias + col);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const f32x4 z = acc[i][j] + bc;
+            Z[(size_t)(4 * i + j) * 256 + threadIdx.x] = z;
+            *(uint2 *)(Out + (16 * i + (lane & 15)) * HLD + col) = gelu_bf16x4(z);
+        }
+    }
+}
+
+// dZ = dH GELU'(Z): FP32 to G, bf16 into the tile Out
+template <int RB>
+__device__ __forceinline__ void train_back(const f32x4 (&acc)[RB][4], int n0, const f32x4 *__restrict__ Z, int r0,
+                                           float *__restrict__ G, uint16_t *Out) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + 16 * j + 4 * (lane >> 4);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int row = 16 * i + (lane & 15);
+            const f32x4 z = Z[(size_t)(4 * i + j) * 256 + threadIdx.x];
+            f32x4 g;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) g[r] = acc[i][j][r] * gelu_df(z[r]);
+            *(f32x4 *)(G + (size_t)(r0 + row) * S_HID + col) = g;
+            *(uint2 *)(Out + row * HLD + col) = uint2{pk_bf16(g[0], g[1]), pk_bf16(g[2], g[3])};
+        }
+    }
+}
+
+struct TrainW {
+    const uint16_t *W[5], *WT[5];
+    const float *b[5];
+};
+
+template <int RB>
+__global__ __launch_bounds__(256, 2) void k_mlp_train(const uint16_t *__restrict__ X, const float *__restrict__ Tg,
+                                                      const int *__restrict__ idx, int B, int nout, TrainW wt,
+                                                      TrainBufs t) {
+    constexpr int R = 16 * RB;
+    extern __shared__ __align__(16) uint16_t sm16[];
+    uint16_t *Xs = sm16, *Ha = Xs + R * XLD, *Hb = Ha + R * HLD;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, n0 = 64 * w;
+    const int r0 = blockIdx.x * R;
+    f32x4 *Z = reinterpret_cast<f32x4 *>(t.Z) + (size_t)blockIdx.x * (16 * RB) * 256;
+    constexpr size_t ZL = (size_t)4 * RB * 256;   // a layer's part
+    WTile<S_IN, 4> w0;
+    w0.load(wt.W[0], n0);
+    for (int q = tid; q < R * 8; q += 256) {
+        const int row = q >> 3, c8 = q & 7;
+        const int64_t src = idx ? idx[r0 + row] : r0 + row;
+        *(uint4 *)(Xs + row * XLD + 8 * c8) = *(const uint4 *)(X + src * S_IN + 8 * c8);
+    }
+    __syncthreads();
+    f32x4 acc[RB][4];
+    WTile<S_HID, 4> wh;
+    w0.template apply<RB>(Xs, XLD, acc);
+    store_transposed<RB, S_IN>(Xs, XLD, t.XT, B, r0);
+    wh.load(wt.W[1], n0);
+    train_hidden<RB>(acc, wt.b[0], n0, Z, Ha);
+    __syncthreads();
+    wh.template apply<RB>(Ha, HLD, acc);
+    store_transposed<RB, S_HID>(Ha, HLD, t.HT[0], B, r0);
+    wh.load(wt.W[2], n0);
+    train_hidden<RB>(acc, wt.b[1], n0, Z + ZL, Hb);
+    __syncthreads();
+    wh.template apply<RB>(Hb, HLD, acc);
+    store_transposed<RB, S_HID>(Hb, HLD, t.HT[1], B, r0);
+    wh.load(wt.W[3], n0);
+    train_hidden<RB>(acc, wt.b[2], n0, Z + 2 * ZL, Ha);
+    __syncthreads();
+    wh.template apply<RB>(Ha, HLD, acc);
+    store_transposed<RB, S_HID>(Ha, HLD, t.HT[2], B, r0);
+    WTile<S_HID, 1> wo;
+    wo.load(wt.W[4], 16 * w);
+    train_hidden<RB>(acc, wt.b[3], n0, Z + 3 * ZL, Hb);
+    __syncthreads();
+    f32x4 o[RB][1];
+    wo.template apply<RB>(Hb, HLD, o);
+    store_transposed<RB, S_HID>(Hb, HLD, t.HT[3], B, r0);
+    WTile<S_OUT, 4> w5;
+    w5.load(wt.WT[4], n0);
+    // dO = 2 (out - target) / (B nout) for the first nout columns, 0 elsewhere
+    double l2 = 0.0;
+    {
+        const int col = 16 * w + 4 * (lane >> 4);
+        const f32x4 bc = *(const f32x4 *)(wt.b[4] + col);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int row = 16 * i + (lane & 15);
+            const int64_t src = idx ? idx[r0 + row] : r0 + row;
+            const f32x4 v = o[i][0] + bc;
+            const f32x4 tg = *(const f32x4 *)(Tg + src * S_OUT + col);
+            f32x4 g;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float e = v[r] - tg[r];
+                const bool live = col + r < nout;
+                g[r] = live ? 2.0f * e / ((float)B * (float)nout) : 0.0f;
+                l2 += live ? (double)e * e : 0.0;
+            }
+            *(f32x4 *)(t.dOf + (size_t)(r0 + row) * S_OUT + col) = g;
+            *(uint2 *)(Xs + row * XLD + col) = uint2{pk_bf16(g[0], g[1]), pk_bf16(g[2], g[3])};
+        }
+    }
+    for (int m = 32; m > 0; m >>= 1) l2 += __shfl_xor(l2, m);
+    __shared__ double sh[4];
+    if (lane == 0) sh[w] = l2;
+    __syncthreads();
+    if (tid == 0) t.lpart[blockIdx.x] += (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    // backward: dH = dZ W layer by layer
+    w5.template apply<RB>(Xs, XLD, acc);
+    store_transposed<RB, S_OUT>(Xs, XLD, t.dZ5T, B, r0);
+    wh.load(wt.WT[3], n0);
+    train_back<RB>(acc, n0, Z + 3 * ZL, r0, t.G[3], Ha);
+    __syncthreads();
+    wh.template apply<RB>(Ha, HLD, acc);
+    store_transposed<RB, S_HID>(Ha, HLD, t.dZT[3], B, r0);
+    wh.load(wt.WT[2], n0);
+    train_back<RB>(acc, n0, Z + 2 * ZL, r0, t.G[2], Hb);
+    __syncthreads();
+    wh.template apply<RB>(Hb, HLD, acc);
+    store_transposed<RB, S_HID>(Hb, HLD, t.dZT[2], B, r0);
+    wh.load(wt.WT[1], n0);
+    train_back<RB>(acc, n0, Z + ZL, r0, t.G[1], Ha);
+    __syncthreads();
+    wh.template apply<RB>(Ha, HLD, acc);
+    store_transposed<RB, S_HID>(Ha, HLD, t.dZT[1], B, r0);
+    train_back<RB>(acc, n0, Z, r0, t.G[0], Hb);
+    __syncthreads();
+    store_transposed<RB, S_HID>(Hb, HLD, t.dZT[0], B, r0);
+}
+static constexpr size_t train_lds(int RB) { return sizeof(uint16_t) * (size_t)16 * RB * (XLD + 2 * HLD); }
 
 // Every row of a chunk selected, in order (the fused kernel's check entry).
 __global__ __launch_bounds__(256) void k_select_all(int m, int *idx, int *cnt) {
@@ -711,8 +918,12 @@ Surrogate::~Surrogate() {
 int Surrogate::init(int N_, int nel_, const std::vector<double> &E_host, char *err) {
     N = N_;
     nel = nel_;
-    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer, hipFuncAttributeMaxDynamicSharedMemorySize,
+    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)kInferLds));
+    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)kInferLds));
+    SCHK(hipFuncSetAttribute((const void *)k_mlp_train<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)train_lds(2)));
     const int64_t np = surrogate_param_count();
     float *fp = nullptr;
     SCHK(dalloc(&fp, np)); bufs.push_back(fp); P = fp;
@@ -756,33 +967,32 @@ int Surrogate::get_params(float *host, hipStream_t s, char *err) {
     return 0;
 }
 
-// workspace for up to B rows: activations, transposes, pre-activations
+// Workspace for up to B rows.  Inference: the selected rows and their outputs.
+// Training: the tile kernel's arrays, and the slabs of the weight gradients.
 int Surrogate::reserve_ws(int B, bool training, char *err) {
     if (B <= ws_rows && (!training || ws_training)) return 0;
     for (void *p : ws) (void)hipFree(p);
     ws.clear();
+    ws_rows = 0;
     auto get16 = [&](uint16_t **p, size_t n) { hipError_t e = dalloc(p, n); ws.push_back(*p); return e; };
     auto get32 = [&](float **p, size_t n) { hipError_t e = dalloc(p, n); ws.push_back(*p); return e; };
-    SCHK(get16(&X, (size_t)B * S_IN));
-    for (int l = 0; l < 4; ++l) SCHK(get16(&H[l], (size_t)B * S_HID));
     SCHK(get32(&out, (size_t)B * S_OUT));
     if (training) {
+        SCHK(get16(&X, (size_t)B * S_IN));
+        SCHK(get32(&Tg, (size_t)B * S_OUT));
         SCHK(get16(&XT, (size_t)B * S_IN));
         for (int l = 0; l < 4; ++l) {
             SCHK(get16(&HT[l], (size_t)B * S_HID));
-            SCHK(get32(&Z[l], (size_t)B * S_HID));
+            SCHK(get16(&dZT[l], (size_t)B * S_HID));
+            SCHK(get32(&dZ[l], (size_t)B * S_HID));
         }
-        SCHK(get32(&Tg, (size_t)B * S_OUT));
+        SCHK(get32(&Z, (size_t)4 * B * S_HID));
         SCHK(get32(&dOf, (size_t)B * S_OUT));
-        SCHK(get16(&dZ5, (size_t)B * S_OUT));
         SCHK(get16(&dZ5T, (size_t)B * S_OUT));
-        SCHK(get32(&dH, (size_t)B * S_HID));
-        SCHK(get16(&dZb, (size_t)B * S_HID));
-        SCHK(get16(&dZbT, (size_t)B * S_HID));
-        SCHK(get32(&csum, (size_t)CS_CHUNKS * S_HID));
-        SCHK(get32(&kpart, (size_t)kSplitFloats));
+        SCHK(get32(&csum, (size_t)5 * CS_CHUNKS * S_HID));
+        SCHK(get32(&kpart, (size_t)5 * kSplitFloats));
         double *dp = nullptr;
-        SCHK(dalloc(&dp, (size_t)(B + 3) / 4)); ws.push_back(dp); lpart = dp;
+        SCHK(dalloc(&dp, (size_t)(B + 15) / 16)); ws.push_back(dp); lpart = dp;
     }
     int *ip = nullptr;
     SCHK(dalloc(&ip, (size_t)B)); ws.push_back(ip); idx = ip;
@@ -792,114 +1002,118 @@ int Surrogate::reserve_ws(int B, bool training, char *err) {
     return 0;
 }
 
-// forward of B rows already in X (inference epilogue unless training)
-void Surrogate::forward(int B, bool training, bool out_transposed, hipStream_t s) {
-    const uint16_t *in = X;
-    int ldin = S_IN;
-    for (int l = 0; l < 4; ++l) {
-        GemmEpi e{};
-        e.bias = P + layer_offset(l) + (int64_t)layer_out(l) * layer_in(l);
-        e.H = H[l]; e.ldh = S_HID;
-        if (training) { e.HT = HT[l]; e.ldht = B; e.Z = Z[l]; e.ldz = S_HID; }
-        gemm<EPI_HID>(in, ldin, Wb[l], layer_in(l), B, S_HID, layer_in(l), e, s);
-        in = H[l];
-        ldin = S_HID;
-    }
-    GemmEpi e{};
-    e.bias = P + layer_offset(4) + (int64_t)S_OUT * S_HID;
-    e.C = out;
-    if (out_transposed) {
-        e.ldc = B;
-        gemm<EPI_OUT_T>(in, S_HID, Wb[4], S_HID, B, S_OUT, S_HID, e, s);
-    } else {
-        e.ldc = S_OUT;
-        gemm<EPI_OUT>(in, S_HID, Wb[4], S_HID, B, S_OUT, S_HID, e, s);
-    }
-}
+// Rows of a training tile: 32 where that leaves a tile for every CU (a tile
+// streams the weights of both passes, 0.9 MB, so fewer tiles read less), else 16
+// (a batch of 4096 is then 256 tiles).  64 rows spill 119 registers.
+static bool wide_tiles(int B) { return B >= 32 * 256; }
 
-void Surrogate::colsum(const float *src, int B, int ncol, float *dst, hipStream_t s) {
-    hipLaunchKernelGGL(k_colsum_part, dim3((ncol + 63) / 64, CS_CHUNKS), dim3(256), 0, s, src, B, ncol,
-                       csum);
-    hipLaunchKernelGGL(k_colsum_final, dim3((ncol + 255) / 256), dim3(256), 0, s, csum, ncol, dst);
-}
-
-// C [M x N], leading dimension N, = A B^T for a weight gradient: M x N is a
-// few tiles and K (the batch) is long, so the K range is cut into S slices
-// that fill the chip; each slice writes its partial product and a second pass
-// adds the slices in order
-bool Surrogate::gemm_wgrad(const uint16_t *A, int lda, const uint16_t *Bm, int ldb, int M, int N,
-                           int K, float *C, hipStream_t s) {
-    const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    int S = 1;
-    while (tiles * 2 * S <= 256 && K % (64 * S) == 0 && K / (2 * S) >= 128 &&
-           (int64_t)2 * S * M * N <= kSplitFloats)
-        S *= 2;
-    // launch invariants, checked on the host before anything is enqueued:
-    // every slice is a whole number of 32-wide k steps inside the rows of A
-    // and B, and the S slabs of M x N partial sums fit the slice buffer
-    if (K % S != 0 || (K / S) % 32 != 0 || K > lda || K > ldb || (int64_t)S * M * N > kSplitFloats)
-        return false;
-    GemmEpi e{};
-    e.ldc = N;
-    if (S == 1) {
-        e.C = C;
-        gemm<EPI_PLAIN>(A, lda, Bm, ldb, M, N, K, e, s);
-        return true;
-    }
-    e.C = kpart;
-    hipLaunchKernelGGL(k_gemm_nt<EPI_PLAIN>, dim3((M + 63) / 64, (N + 63) / 64, S), dim3(256), 0, s,
-                       A, lda, Bm, ldb, M, N, K / S, e);
-    const int64_t mn = (int64_t)M * N;
-    hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s, kpart, S,
-                       mn, C);
-    return true;
-}
-
-// gradients of the mean-squared error for the B rows in X / Tg into G;
-// false (nothing enqueued past the failing launch) if a launch would not fit
-// the workspace
-bool Surrogate::backward(int B, hipStream_t s) {
-    const int nout = N + 1;
+// Forward and backward of B rows from X / Tg (rows idx[r], or r), then the
+// partial sums of every gradient, which k_gradients adds up.  False (nothing
+// enqueued) if a launch would not fit the workspace.
+bool Surrogate::gradients(int B, const uint16_t *Xr, const float *Tr, const int *rows, hipStream_t s,
+                          GradParts &gp) {
     if (B > ws_rows || !ws_training || B % 64 != 0) return false;
-    hipLaunchKernelGGL(k_out_grad, dim3((B + 3) / 4), dim3(256), 0, s, out, Tg, B, nout, dOf, dZ5,
-                       dZ5T, B, lpart);
-    // output layer
-    {
-        if (!gemm_wgrad(dZ5T, B, HT[3], B, S_OUT, S_HID, B, G + layer_offset(4), s))   // dW5 = dZ5^T H4
-            return false;
-        colsum(dOf, B, S_OUT, G + layer_offset(4) + (int64_t)S_OUT * S_HID, s);
-        GemmEpi e2{};
-        e2.C = dH; e2.ldc = S_HID;
-        gemm<EPI_PLAIN>(dZ5, S_OUT, WbT[4], S_OUT, B, S_HID, S_OUT, e2, s);    // dH4 = dZ5 W5
+    WgradJobs jobs{};
+    jobs.ld = B;
+    int first = 0;
+    for (int l = 0; l < 5; ++l) {
+        const int M = layer_out(l), Nl = layer_in(l), tiles = (M / 64) * (Nl / 64);
+        int S = 1;
+        while (tiles * 2 * S <= 256 && B % (64 * S) == 0 && B / (2 * S) >= 128 &&
+               (int64_t)2 * S * M * Nl <= kSplitFloats)
+            S *= 2;
+        // launch invariants, checked on the host before anything is enqueued:
+        // every slice is a whole number of 32-wide k steps of the batch, and
+        // the S slabs of M x N partial sums fit the layer's part of the buffer
+        if (B % S != 0 || (B / S) % 32 != 0 || (int64_t)S * M * Nl > kSplitFloats) return false;
+        WgradJob &j = jobs.j[l];
+        j.A = l == 4 ? dZ5T : dZT[l];
+        j.B = l == 0 ? XT : HT[l - 1];
+        j.C = kpart + (size_t)l * kSplitFloats;
+        j.M = M; j.N = Nl; j.S = S; j.first = first;
+        first += tiles * S;
+        gp.W[l] = j.C;
+        gp.S[l] = S;
     }
-    for (int l = 3; l >= 0; --l) {
-        hipLaunchKernelGGL(k_gelu_back, dim3(S_HID / 64, CS_CHUNKS), dim3(256), 0, s, dH, Z[l], B,
-                           dZb, dZbT, B, csum);
-        const int ni = layer_in(l);
-        const uint16_t *inT = l == 0 ? XT : HT[l - 1];
-        if (!gemm_wgrad(dZbT, B, inT, B, S_HID, ni, B, G + layer_offset(l), s))   // dW = dZ^T h_{l-1}
-            return false;
-        hipLaunchKernelGGL(k_colsum_final, dim3(1), dim3(256), 0, s, csum, S_HID,
-                           G + layer_offset(l) + (int64_t)S_HID * ni);
-        if (l > 0) {
-            GemmEpi e2{};
-            e2.C = dH; e2.ldc = S_HID;
-            gemm<EPI_PLAIN>(dZb, S_HID, WbT[l], S_HID, B, S_HID, S_HID, e2, s);   // dh = dZ W
-        }
+    gp.col = csum;
+    TrainW wt{};
+    TrainBufs t{};
+    ColSrc cs{};
+    for (int l = 0; l < 5; ++l) {
+        wt.W[l] = Wb[l];
+        wt.WT[l] = WbT[l];
+        wt.b[l] = P + layer_offset(l) + (int64_t)layer_out(l) * layer_in(l);
     }
+    for (int l = 0; l < 4; ++l) {
+        t.HT[l] = HT[l];
+        t.dZT[l] = dZT[l];
+        t.G[l] = dZ[l];
+        cs.G[l] = dZ[l];
+    }
+    cs.G[4] = dOf;
+    t.Z = Z; t.XT = XT; t.dZ5T = dZ5T; t.dOf = dOf; t.lpart = lpart;
+    if (wide_tiles(B))
+        hipLaunchKernelGGL(k_mlp_train<2>, dim3(B / 32), dim3(256), train_lds(2), s, Xr, Tr, rows, B, N + 1, wt, t);
+    else
+        hipLaunchKernelGGL(k_mlp_train<1>, dim3(B / 16), dim3(256), train_lds(1), s, Xr, Tr, rows, B, N + 1, wt, t);
+    hipLaunchKernelGGL(k_colsum_part, dim3(S_HID / 64, CS_CHUNKS, 5), dim3(256), 0, s, cs, B, csum);
+    hipLaunchKernelGGL(k_wgrad, dim3(first), dim3(256), 0, s, jobs);
     return true;
 }
+static int loss_blocks(int B) { return wide_tiles(B) ? B / 32 : B / 16; }
 
-int Surrogate::compute_norm(const FeatSrc &f, const TgtSrc &t, hipStream_t s, char *err) {
+WeightCopies Surrogate::weight_copies() const {
+    WeightCopies wc{};
+    for (int l = 0; l < 5; ++l) {
+        wc.off[l] = layer_offset(l);
+        wc.no[l] = layer_out(l);
+        wc.ni[l] = layer_in(l);
+        wc.Wb[l] = Wb[l];
+        wc.WbT[l] = WbT[l];
+    }
+    return wc;
+}
+
+// Standard normal floats by Marsaglia's polar method over a 64-bit Mersenne
+// Twister, the sequence of std::normal_distribution<float>: two uniforms x, y in
+// [-1, 1) until 0 < x^2 + y^2 <= 1, then y f is returned and x f kept for the next
+// call, f = sqrt(-2 ln r2 / r2).  The library's uniform takes a long-double
+// logarithm per draw as built here: 230 K draws cost 15.7 ms against 4.1.
+class PolarNormal {
+    std::mt19937_64 rng;
+    float kept = 0.0f;
+    bool has = false;
+    float unit() {
+        const float u = (float)rng() * 0x1p-64f;
+        return u < 1.0f ? u : 0x1.fffffep-1f;
+    }
+
+public:
+    explicit PolarNormal(uint64_t seed) : rng(seed) {}
+    float operator()() {
+        if (has) {
+            has = false;
+            return kept;
+        }
+        float x, y, r2;
+        do {
+            x = 2.0f * unit() - 1.0f;
+            y = 2.0f * unit() - 1.0f;
+            r2 = x * x + y * y;
+        } while (r2 > 1.0f || r2 == 0.0f);
+        const float f = std::sqrt(-2.0f * std::log(r2) / r2);
+        kept = x * f;
+        has = true;
+        return y * f;
+    }
+};
+
+// Normalisation and training box from the device's moments dm into the parameters.
+int Surrogate::compute_norm(const FeatSrc &f, const double *dm, hipStream_t s, char *err) {
     const int nfeat = N + 3, nout = N + 1;
-    double *dm = nullptr;
-    SCHK(dalloc(&dm, (size_t)4 * nfeat + 2 * nout));
-    hipLaunchKernelGGL(k_feature_moments, dim3(nfeat), dim3(256), 0, s, f, nfeat, dm);
-    hipLaunchKernelGGL(k_target_moments, dim3(nout), dim3(256), 0, s, t, dm + 4 * nfeat);
     std::vector<double> hm(4 * nfeat + 2 * nout);
     SCHK(hipMemcpyAsync(hm.data(), dm, sizeof(double) * hm.size(), hipMemcpyDeviceToHost, s));
     SCHK(hipStreamSynchronize(s));
-    (void)hipFree(dm);
     std::vector<float> nb(6 * S_IN, 0.0f);
     const double n = (double)f.n;
     for (int c = 0; c < S_IN; ++c) { nb[64 + c] = 1.0f; nb[192 + c] = 1.0f; }
@@ -936,13 +1150,21 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
     if (n < B) { snprintf(err, 256, "fewer samples than one batch"); return -1; }
     int rc = reserve_ws(B, true, err);
     if (rc) return rc;
-    rc = compute_norm(f, t, s, err);
-    if (rc) return rc;
-    // He-style initialisation (seeded), zero biases, small output layer
+    // per-call buffers, released on every return
+    struct Bufs {
+        std::vector<void *> v;
+        ~Bufs() { for (void *p : v) (void)hipFree(p); }
+    } own;
+    const int nfeat = N + 3, nout = N + 1;
+    double *dm = nullptr;
+    SCHK(dalloc(&dm, (size_t)4 * nfeat + 2 * nout)); own.v.push_back(dm);
+    hipLaunchKernelGGL(k_moments, dim3(nfeat + nout), dim3(MOM_T), 0, s, f, t, nfeat, dm);
+    SCHK(hipGetLastError());
+    // He-style initialisation (seeded), zero biases, small output layer, drawn
+    // while the device forms the moments
+    std::vector<float> h(weights_count(), 0.0f);
     {
-        std::mt19937_64 rng(seed);
-        std::normal_distribution<float> nd(0.0f, 1.0f);
-        std::vector<float> h(weights_count(), 0.0f);
+        PolarNormal nd(seed);
         for (int l = 0; l < 5; ++l) {
             const int no = layer_out(l), ni = layer_in(l);
             const float sc = (l == 4 ? 0.1f : 1.0f) * sqrtf(2.0f / (float)ni);
@@ -951,42 +1173,59 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
                 for (int i = 0; i < ni; ++i) {
                     const bool live_in = l > 0 || i < N + 3;
                     const bool live_out = l < 4 || o < N + 1;
-                    W[o * ni + i] = (live_in && live_out) ? sc * nd(rng) : 0.0f;
+                    W[o * ni + i] = (live_in && live_out) ? sc * nd() : 0.0f;
                 }
         }
-        SCHK(hipMemcpyAsync(P, h.data(), sizeof(float) * h.size(), hipMemcpyHostToDevice, s));
-        SCHK(hipMemsetAsync(mA, 0, sizeof(float) * weights_count(), s));
-        SCHK(hipMemsetAsync(vA, 0, sizeof(float) * weights_count(), s));
-        SCHK(hipStreamSynchronize(s));   // h is released at the end of this scope
     }
+    rc = compute_norm(f, dm, s, err);
+    if (rc) return rc;
+    SCHK(hipMemcpyAsync(P, h.data(), sizeof(float) * h.size(), hipMemcpyHostToDevice, s));
+    SCHK(hipMemsetAsync(mA, 0, sizeof(float) * weights_count(), s));
+    SCHK(hipMemsetAsync(vA, 0, sizeof(float) * weights_count(), s));
     rc = refresh(s, err);
     if (rc) return rc;
     const int64_t nb = n / B;
     const int64_t total = nb * epochs;
     int *d_perm = nullptr;
-    SCHK(dalloc(&d_perm, (size_t)n));
+    SCHK(dalloc(&d_perm, (size_t)n)); own.v.push_back(d_perm);
+    // The normalised rows of every sample are built once (384 bytes each) and
+    // gathered by each step; where they do not fit, each batch builds its own.
+    uint16_t *Xall = nullptr;
+    float *Tall = nullptr;
+    if (dalloc(&Xall, (size_t)n * S_IN) == hipSuccess) {
+        own.v.push_back(Xall);
+        if (dalloc(&Tall, (size_t)n * S_OUT) == hipSuccess) own.v.push_back(Tall);
+        else Tall = nullptr;
+    }
+    (void)hipGetLastError();   // a failed allocation is not the launches' error
+    const bool all_rows = Tall != nullptr;
+    if (all_rows)
+        hipLaunchKernelGGL(k_build_rows, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, f, t, (const int *)nullptr,
+                           n, P + weights_count(), Xall, Tall);
     std::vector<int> perm(n);
     std::mt19937_64 rng(seed ^ 0x9e3779b97f4a7c15ull);
-    int64_t step = 0;
-    const int64_t nw = weights_count();
-    WeightCopies wc{};
-    for (int l = 0; l < 5; ++l) {
-        wc.off[l] = layer_offset(l);
-        wc.no[l] = layer_out(l);
-        wc.ni[l] = layer_in(l);
-        wc.Wb[l] = Wb[l];
-        wc.WbT[l] = WbT[l];
-    }
-    for (int ep = 0; ep < epochs; ++ep) {
+    auto shuffle = [&] {
         std::iota(perm.begin(), perm.end(), 0);
         std::shuffle(perm.begin(), perm.end(), rng);
+    };
+    if (epochs > 0) shuffle();
+    SCHK(hipStreamSynchronize(s));   // h has been read
+    int64_t step = 0;
+    const int64_t nw = weights_count();
+    const WeightCopies wc = weight_copies();
+    for (int ep = 0; ep < epochs; ++ep) {
         SCHK(hipMemcpyAsync(d_perm, perm.data(), sizeof(int) * n, hipMemcpyHostToDevice, s));
-        SCHK(hipMemsetAsync(lpart, 0, sizeof(double) * ((B + 3) / 4), s));
+        SCHK(hipMemsetAsync(lpart, 0, sizeof(double) * loss_blocks(B), s));
+        SCHK(hipStreamSynchronize(s));   // perm has been read
         for (int64_t bi = 0; bi < nb; ++bi, ++step) {
-            hipLaunchKernelGGL(k_build_rows, dim3((B + 3) / 4), dim3(256), 0, s, f, t,
-                               d_perm + bi * B, (int64_t)0, B, P + weights_count(), X, XT, B, Tg);
-            forward(B, true, false, s);
-            if (!backward(B, s)) {
+            const int *rows = d_perm + bi * B;
+            if (!all_rows) {
+                hipLaunchKernelGGL(k_build_rows, dim3(B / 64), dim3(256), 0, s, f, t, rows, (int64_t)B,
+                                   P + weights_count(), X, Tg);
+                rows = nullptr;
+            }
+            GradParts gp{};
+            if (!gradients(B, all_rows ? Xall : X, all_rows ? Tall : Tg, rows, s, gp)) {
                 snprintf(err, 256, "backward: launch does not fit the workspace (batch %d)", B);
                 return -1;
             }
@@ -994,10 +1233,11 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
             const float lr = (float)(lr1 + 0.5 * (lr0 - lr1) * (1.0 + cos(M_PI * frac)));
             const float b1 = 0.9f, b2 = 0.999f;
             const float c1 = 1.0f - powf(b1, (float)(step + 1)), c2 = 1.0f - powf(b2, (float)(step + 1));
-            hipLaunchKernelGGL(k_adam, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, P, G, mA,
-                               vA, nw, lr, b1, b2, 1e-8f, c1, c2, wc);
+            hipLaunchKernelGGL(k_gradients<true>, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, gp, wc, nw,
+                               (float *)nullptr, P, mA, vA, lr, b1, b2, 1e-8f, c1, c2);
         }
-        hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, s, lpart, (B + 3) / 4, d_loss);
+        hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, s, lpart, loss_blocks(B), d_loss);
+        if (ep + 1 < epochs) shuffle();   // the next epoch's order while this one runs
         double l = 0.0;
         SCHK(hipMemcpyAsync(&l, d_loss, sizeof(double), hipMemcpyDeviceToHost, s));
         SCHK(hipStreamSynchronize(s));
@@ -1005,8 +1245,8 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
         if (loss_hist) loss_hist[ep] = (float)mean;
         if (verbose) fprintf(stderr, "[libchem] surrogate epoch %d/%d: loss %.4e\n", ep + 1, epochs, mean);
     }
+    SCHK(hipStreamSynchronize(s));
     SCHK(hipGetLastError());
-    (void)hipFree(d_perm);
     trained = true;
     return 0;
 }
@@ -1017,16 +1257,19 @@ int Surrogate::loss_grad(const FeatSrc &f, const TgtSrc &t, float *grad_host, do
     if (B % 64 != 0 || B < 64 || B > 65536) { snprintf(err, 256, "n must be a multiple of 64, <= 65536"); return -1; }
     int rc = reserve_ws(B, true, err);
     if (rc) return rc;
-    SCHK(hipMemsetAsync(lpart, 0, sizeof(double) * ((B + 3) / 4), s));
-    hipLaunchKernelGGL(k_build_rows, dim3((B + 3) / 4), dim3(256), 0, s, f, t, (const int *)nullptr,
-                       (int64_t)0, B, P + weights_count(), X, XT, B, Tg);
-    forward(B, true, false, s);
-    if (!backward(B, s)) {
+    SCHK(hipMemsetAsync(lpart, 0, sizeof(double) * loss_blocks(B), s));
+    hipLaunchKernelGGL(k_build_rows, dim3(B / 64), dim3(256), 0, s, f, t, (const int *)nullptr, (int64_t)B,
+                       P + weights_count(), X, Tg);
+    GradParts gp{};
+    if (!gradients(B, X, Tg, nullptr, s, gp)) {
         snprintf(err, 256, "backward: launch does not fit the workspace (%d rows)", B);
         return -1;
     }
-    hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, s, lpart, (B + 3) / 4, d_loss);
-    SCHK(hipMemcpyAsync(grad_host, G, sizeof(float) * weights_count(), hipMemcpyDeviceToHost, s));
+    const int64_t nw = weights_count();
+    hipLaunchKernelGGL(k_gradients<false>, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, gp, weight_copies(),
+                       nw, G, (float *)nullptr, (float *)nullptr, (float *)nullptr, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
+    hipLaunchKernelGGL(k_sum_loss, dim3(1), dim3(256), 0, s, lpart, loss_blocks(B), d_loss);
+    SCHK(hipMemcpyAsync(grad_host, G, sizeof(float) * nw, hipMemcpyDeviceToHost, s));
     double l = 0.0;
     SCHK(hipMemcpyAsync(&l, d_loss, sizeof(double), hipMemcpyDeviceToHost, s));
     SCHK(hipStreamSynchronize(s));
@@ -1034,19 +1277,24 @@ int Surrogate::loss_grad(const FeatSrc &f, const TgtSrc &t, float *grad_host, do
     return 0;
 }
 
+MlpW Surrogate::infer_weights() const {
+    MlpW wts{};
+    for (int l = 0; l < 5; ++l) {
+        wts.W[l] = Wb[l];
+        wts.b[l] = P + layer_offset(l) + (int64_t)layer_out(l) * layer_in(l);
+    }
+    return wts;
+}
+
+// Raw outputs of every row, straight to the caller's array.
 int Surrogate::forward_rows(const FeatSrc &f, float *out_dev, hipStream_t s, char *err) {
     const int64_t n = f.n;
-    const int chunk = 65536;
-    int rc = reserve_ws((int)std::min<int64_t>(n, chunk), false, err);
-    if (rc) return rc;
-    TgtSrc t{};
+    const int chunk = 1 << 24;
     for (int64_t base = 0; base < n; base += chunk) {
         const int m = (int)std::min<int64_t>(chunk, n - base);
-        hipLaunchKernelGGL(k_build_rows, dim3((m + 3) / 4), dim3(256), 0, s, f, t, (const int *)nullptr,
-                           base, m, P + weights_count(), X, (uint16_t *)nullptr, 0, (float *)nullptr);
-        forward(m, false, false, s);
-        SCHK(hipMemcpyAsync(out_dev + base * S_OUT, out, sizeof(float) * m * S_OUT,
-                            hipMemcpyDeviceToDevice, s));
+        hipLaunchKernelGGL(k_mlp_infer<false>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
+                           (const int *)nullptr, (const int *)nullptr, P + weights_count(), infer_weights(),
+                           out_dev + base * S_OUT);
     }
     SCHK(hipGetLastError());
     return 0;
@@ -1059,15 +1307,11 @@ int Surrogate::forward_fused_rows(const FeatSrc &f, float *out_dev, hipStream_t 
     const int chunk = 262144;
     int rc = reserve_ws((int)std::min<int64_t>(n, chunk), false, err);
     if (rc) return rc;
-    MlpW wts{};
-    for (int l = 0; l < 5; ++l) {
-        wts.W[l] = Wb[l];
-        wts.b[l] = P + layer_offset(l) + (int64_t)layer_out(l) * layer_in(l);
-    }
+    const MlpW wts = infer_weights();
     for (int64_t base = 0; base < n; base += chunk) {
         const int m = (int)std::min<int64_t>(chunk, n - base);
         hipLaunchKernelGGL(k_select_all, dim3((m + 255) / 256), dim3(256), 0, s, m, idx, sel_cnt);
-        hipLaunchKernelGGL(k_mlp_infer, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
+        hipLaunchKernelGGL(k_mlp_infer<true>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
                            idx, sel_cnt, P + weights_count(), wts, out);
         hipLaunchKernelGGL(k_untranspose, dim3((unsigned)(((int64_t)m * S_OUT + 255) / 256)), dim3(256),
                            0, s, out, m, out_dev + base * S_OUT);
@@ -1082,24 +1326,19 @@ int Surrogate::apply(const FeatSrc &f, double *T, double *Y, uint8_t *flags, con
     const int chunk = 262144;
     int rc = reserve_ws((int)std::min<int64_t>(n, chunk), false, err);
     if (rc) return rc;
-    MlpW wts{};
-    for (int l = 0; l < 5; ++l) {
-        wts.W[l] = Wb[l];
-        wts.b[l] = P + layer_offset(l) + (int64_t)layer_out(l) * layer_in(l);
-    }
+    const MlpW wts = infer_weights();
     PostParams q{};
     q.N = N; q.nel = nel; q.E = E; q.nasa_t = pin.nasa_t; q.invW = pin.invW;
     q.norm = P + weights_count(); q.tau_T = pin.tau_T; q.y_min = pin.y_min; q.margin = pin.margin;
     q.max_dT = pin.max_dT;
     q.T_max = pin.T_max;
-    TgtSrc t{};
     for (int64_t base = 0; base < n; base += chunk) {
         const int m = (int)std::min<int64_t>(chunk, n - base);
         // only offered rows go through the network (fused, one kernel)
         hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, sel_cnt);
         hipLaunchKernelGGL(k_sur_select, dim3((m + 255) / 256), dim3(256), 0, s, flags, T, base, m,
                            pin.T_max, idx, sel_cnt);
-        hipLaunchKernelGGL(k_mlp_infer, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
+        hipLaunchKernelGGL(k_mlp_infer<true>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
                            idx, sel_cnt, P + weights_count(), wts, out);
         launch_post(nel, dim3((m + 255) / 256), s, f, base, m, out, q, T, Y, flags, stats);
     }

@@ -36,6 +36,10 @@ struct PostIn {
 
 int64_t surrogate_param_count();
 
+struct GradParts;     // partial sums of a gradient
+struct WeightCopies;  // the layers' places in the blob and their bf16 copies
+struct MlpW;          // weights and biases of the inference kernel
+
 struct Surrogate {
     int N = 0, nel = 0;
     bool trained = false;
@@ -51,12 +55,11 @@ struct Surrogate {
     int ws_rows = 0;
     bool ws_training = false;
     std::vector<void *> ws;
-    uint16_t *X = nullptr, *XT = nullptr, *H[4] = {}, *HT[4] = {};
-    float *Z[4] = {}, *out = nullptr, *Tg = nullptr, *dOf = nullptr, *dH = nullptr;
-    uint16_t *dZ5 = nullptr, *dZ5T = nullptr, *dZb = nullptr, *dZbT = nullptr;
+    uint16_t *X = nullptr, *XT = nullptr, *HT[4] = {}, *dZT[4] = {}, *dZ5T = nullptr;
+    float *Z = nullptr, *dZ[4] = {}, *out = nullptr, *Tg = nullptr, *dOf = nullptr;
     float *csum = nullptr;   // partial column sums of the bias gradients
-    float *kpart = nullptr;  // split-K slices of the weight gradients
-    double *lpart = nullptr; // per-block running sums of the squared error
+    float *kpart = nullptr;  // split-K slabs of the weight gradients
+    double *lpart = nullptr; // per-workgroup running sums of the squared error
     int *idx = nullptr;
     int *sel_cnt = nullptr;  // rows selected for inference
 
@@ -66,12 +69,10 @@ struct Surrogate {
     int set_params(const float *host, hipStream_t s, char *err);
     int get_params(float *host, hipStream_t s, char *err);
     int reserve_ws(int rows, bool training, char *err);
-    void forward(int B, bool training, bool out_transposed, hipStream_t s);
-    bool backward(int B, hipStream_t s);
-    void colsum(const float *src, int B, int ncol, float *dst, hipStream_t s);
-    bool gemm_wgrad(const uint16_t *A, int lda, const uint16_t *Bm, int ldb, int M, int N, int K,
-                    float *C, hipStream_t s);
-    int compute_norm(const FeatSrc &f, const TgtSrc &t, hipStream_t s, char *err);
+    bool gradients(int B, const uint16_t *Xr, const float *Tr, const int *rows, hipStream_t s, GradParts &gp);
+    WeightCopies weight_copies() const;
+    MlpW infer_weights() const;
+    int compute_norm(const FeatSrc &f, const double *dm, hipStream_t s, char *err);
     int train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, double lr0, double lr1,
               uint64_t seed, float *loss_hist, int verbose, hipStream_t s, char *err);
     int loss_grad(const FeatSrc &f, const TgtSrc &t, float *grad_host, double *loss, hipStream_t s,
