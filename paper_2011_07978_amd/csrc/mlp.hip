@@ -50,6 +50,15 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
+// Workgroup barrier for what is in LDS.  __syncthreads also waits for every
+// global access of the wavefront: the weights on their way for the next layer,
+// and stores that nothing in the kernel reads.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // GELU of four values as bfloat16, the bits of f2bf(gelu_f(z)).  The network
 // spends more vector time here than matrix time (about 46 instructions a value
 // with the library's erf, which takes both of its branches in most
@@ -77,10 +86,29 @@ __device__ __forceinline__ uint2 gelu_bf16x4(f32x4 z) {
         bad |= w[r] ^ (w[r] >> 16);
     }
     if (__builtin_amdgcn_ballot_w64((bad & 0xffffu) != 0)) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = f2bf(gelu_f(z[r]));
+        // one copy of the long way for the four: it is rarely taken, and four
+        // copies at every call made the kernels larger than the instruction cache
+#pragma unroll 1
+        for (int r = 0; r < 4; ++r) {
+            const float zr = r == 0 ? z[0] : r == 1 ? z[1] : r == 2 ? z[2] : z[3];
+            const uint32_t v = f2bf(gelu_f(zr));
+            w[0] = r == 0 ? v : w[0];
+            w[1] = r == 1 ? v : w[1];
+            w[2] = r == 2 ? v : w[2];
+            w[3] = r == 3 ? v : w[3];
+        }
     }
     return {(w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
+}
+
+// Place of element (r, k) of a matrix with K columns in operand order: blocks of
+// 16 rows and 32 columns, each lane's eight values in a row, lane after lane, so
+// that an operand is one contiguous kilobyte.  All bf16 operands in memory
+// (weights, their transposes, and what the weight gradients contract) lie so.
+// Row by row, 16 lanes of a load touched 16 cache lines for 16 bytes each, and
+// the address unit bound the tile kernels (forward of 100,003 rows 197 us).
+__host__ __device__ __forceinline__ int64_t op_place(int64_t r, int64_t k, int64_t K) {
+    return (((r >> 4) * (K >> 5) + (k >> 5)) << 9) + ((((k >> 3) & 3) << 4) + (r & 15)) * 8 + (k & 7);
 }
 
 // ------------------------------------------------------------ tile layers ----
@@ -97,12 +125,11 @@ template <int K, int NBK>
 struct WTile {
     bf16x8 w[K / 32][NBK];
     __device__ __forceinline__ void load(const uint16_t *__restrict__ W, int n0) {
-        const int lane = threadIdx.x & 63;
-        const uint16_t *q = W + (size_t)(n0 + (lane & 15)) * K + (lane >> 4) * 8;
+        const uint16_t *q = W + n0 * K + (threadIdx.x & 63) * 8;   // n0 is a multiple of 16
 #pragma unroll
         for (int ks = 0; ks < K / 32; ++ks)
 #pragma unroll
-            for (int j = 0; j < NBK; ++j) w[ks][j] = *(const bf16x8 *)(q + (size_t)16 * j * K + 32 * ks);
+            for (int j = 0; j < NBK; ++j) w[ks][j] = *(const bf16x8 *)(q + (j * (K / 32) + ks) * 512);
     }
     template <int RB>
     __device__ __forceinline__ void apply(const uint16_t *In, int ldi, f32x4 (&acc)[RB][NBK]) const {
@@ -288,31 +315,49 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradJobs jobs) {
     for (int q = 1; q < 5; ++q)
         if ((int)blockIdx.x >= jobs.j[q].first) jb = jobs.j[q];
     const int t = blockIdx.x - jb.first, tm = jb.M / 64, tn = jb.N / 64;
-    const int z = t / (tm * tn), xy = t - z * (tm * tn), x = xy / tn, y = xy - x * tn;
+    const int tiles = tm * tn, z = t / tiles, xy = t - z * tiles;
+    const int x = xy / tn, y = xy - x * tn;
     const int ld = jobs.ld, K = ld / jb.S;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m0 = x * 64 + (w >> 1) * 32, n0 = y * 64 + (w & 1) * 32;
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    const uint16_t *A = jb.A + (size_t)(m0 + r16) * ld + (size_t)z * K + kq;
-    const uint16_t *B = jb.B + (size_t)(n0 + r16) * ld + (size_t)z * K + kq;
+    const uint16_t *A = jb.A + op_place(m0, (int64_t)z * K, ld) + lane * 8;
+    const uint16_t *B = jb.B + op_place(n0, (int64_t)z * K, ld) + lane * 8;
+    const size_t next16 = (size_t)16 * ld;   // to the next 16 rows
     f32x4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        bf16x8 a[2], b[2];
+    // four k steps at a time, the next four on their way (K is a multiple of 32)
+    bf16x8 a[2][4][2], b[2][4][2];
+    auto load = [&](bf16x8 (&la)[4][2], bf16x8 (&lb)[4][2], int k0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            a[i] = *(const bf16x8 *)(A + (size_t)16 * i * ld + k0);
-            b[i] = *(const bf16x8 *)(B + (size_t)16 * i * ld + k0);
-        }
+        for (int u = 0; u < 4; ++u)
+            if (k0 + 32 * u < K) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < 2; ++i) {
+                    la[u][i] = *(const bf16x8 *)(A + i * next16 + (k0 + 32 * u) * 16);
+                    lb[u][i] = *(const bf16x8 *)(B + i * next16 + (k0 + 32 * u) * 16);
+                }
+            }
+    };
+    auto mul = [&](const bf16x8 (&la)[4][2], const bf16x8 (&lb)[4][2], int k0) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int u = 0; u < 4; ++u)
+            if (k0 + 32 * u < K) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(la[u][i], lb[u][j], acc[i][j], 0, 0, 0);
+            }
+    };
+    load(a[0], b[0], 0);
+    for (int k0 = 0; k0 < K; k0 += 256) {
+        load(a[1], b[1], k0 + 128);
+        mul(a[0], b[0], k0);
+        load(a[0], b[0], k0 + 256);
+        mul(a[1], b[1], k0 + 128);
     }
     float *C = jb.C + (size_t)z * jb.M * jb.N;
 #pragma unroll
@@ -321,7 +366,7 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradJobs jobs) {
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                C[(size_t)(m0 + 16 * i + 4 * (lane >> 4) + r) * jb.N + n0 + 16 * j + r16] = acc[i][j][r];
+                C[(size_t)(m0 + 16 * i + 4 * (lane >> 4) + r) * jb.N + n0 + 16 * j + (lane & 15)] = acc[i][j][r];
 }
 
 // where each layer's weights sit in the FP32 blob and their bf16 copies
@@ -381,20 +426,20 @@ __global__ __launch_bounds__(256) void k_gradients(GradParts gp, WeightCopies wc
     if (t < mn) {
         const int o = t / ni, k = t - o * ni;
         const uint16_t b = f2bf(p);
-        wb[t] = b;
-        wbt[(size_t)k * no + o] = b;
+        wb[op_place(o, k, ni)] = b;
+        wbt[op_place(k, o, no)] = b;
     }
 }
 
-// bf16 copies of a layer's weights: Wb [no x ni] and WbT [ni x no]
+// bf16 copies of a layer's weights in operand order: Wb [no x ni] and WbT [ni x no]
 __global__ __launch_bounds__(256) void k_refresh(const float *W, int no, int ni, uint16_t *Wb,
                                                  uint16_t *WbT) {
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= no * ni) return;
     const int o = t / ni, i = t % ni;
     const uint16_t b = f2bf(W[t]);
-    Wb[t] = b;
-    WbT[(size_t)i * no + o] = b;
+    Wb[op_place(o, i, ni)] = b;
+    WbT[op_place(i, o, no)] = b;
 }
 
 // ------------------------------------------------- conservation + gate ----
@@ -635,26 +680,23 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(FeatSrc f, int64_t base, i
             Xs[lane * XLD + c] = v;
         }
     }
-    __syncthreads();
+    lds_barrier();
     f32x4 acc[4][4];
     w0.apply<4>(Xs, XLD, acc);
     WTile<S_HID, 4> wh;
+    WTile<S_HID, 1> wo;
     wh.load(wt.W[1], n0);
     gelu_tile<4>(acc, wt.b[0], n0, Ha);
-    __syncthreads();
-    wh.apply<4>(Ha, HLD, acc);
-    wh.load(wt.W[2], n0);
-    gelu_tile<4>(acc, wt.b[1], n0, Hb);
-    __syncthreads();
-    wh.apply<4>(Hb, HLD, acc);
-    wh.load(wt.W[3], n0);
-    gelu_tile<4>(acc, wt.b[2], n0, Ha);
-    __syncthreads();
-    wh.apply<4>(Ha, HLD, acc);
-    WTile<S_HID, 1> wo;
-    wo.load(wt.W[4], 16 * w);
-    gelu_tile<4>(acc, wt.b[3], n0, Hb);
-    __syncthreads();
+    lds_barrier();
+#pragma unroll
+    for (int l = 1; l < 4; ++l) {   // the last leaves its result in Hb
+        uint16_t *In = (l & 1) ? Ha : Hb, *Out = (l & 1) ? Hb : Ha;
+        wh.apply<4>(In, HLD, acc);
+        if (l < 3) wh.load(wt.W[l + 1], n0);
+        else wo.load(wt.W[4], 16 * w);
+        gelu_tile<4>(acc, wt.b[l], n0, Out);
+        lds_barrier();
+    }
     f32x4 o[4][1];
     wo.apply<4>(Hb, HLD, o);
     const int col = 16 * w + 4 * (lane >> 4);
@@ -686,12 +728,12 @@ static constexpr size_t kInferLds = sizeof(uint16_t) * (size_t)FT * (XLD + 2 * H
 // launches.
 struct TrainBufs {
     float *Z;                              // [tile][layer][block][thread] f32x4
-    uint16_t *XT, *HT[4], *dZT[4], *dZ5T;  // [column][B]
+    uint16_t *XT, *HT[4], *dZT[4], *dZ5T;  // [column][B], operand order
     float *G[4], *dOf;                     // [row][column]
     double *lpart;                         // squared error per workgroup, running
 };
 
-// dst[c][r0 ..] = columns of a tile of 16 RB rows
+// The columns of a tile of 16 RB rows into dst [column][B], in operand order
 template <int RB, int NC>
 __device__ __forceinline__ void store_transposed(const uint16_t *tile, int ld, uint16_t *__restrict__ dst, int B,
                                                  int r0) {
@@ -704,7 +746,7 @@ __device__ __forceinline__ void store_transposed(const uint16_t *tile, int ld, u
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             v[q] = tile[(8 * part + 2 * q) * ld + c] | ((uint32_t)tile[(8 * part + 2 * q + 1) * ld + c] << 16);
-        *(uint4 *)(dst + (size_t)c * B + r0 + 8 * part) = uint4{v[0], v[1], v[2], v[3]};
+        *(uint4 *)(dst + op_place(c, r0 + 8 * part, B)) = uint4{v[0], v[1], v[2], v[3]};
     }
 }
 
@@ -770,30 +812,25 @@ __global__ __launch_bounds__(256, 2) void k_mlp_train(const uint16_t *__restrict
         const int64_t src = idx ? idx[r0 + row] : r0 + row;
         *(uint4 *)(Xs + row * XLD + 8 * c8) = *(const uint4 *)(X + src * S_IN + 8 * c8);
     }
-    __syncthreads();
+    lds_barrier();
     f32x4 acc[RB][4];
     WTile<S_HID, 4> wh;
     w0.template apply<RB>(Xs, XLD, acc);
     store_transposed<RB, S_IN>(Xs, XLD, t.XT, B, r0);
     wh.load(wt.W[1], n0);
     train_hidden<RB>(acc, wt.b[0], n0, Z, Ha);
-    __syncthreads();
-    wh.template apply<RB>(Ha, HLD, acc);
-    store_transposed<RB, S_HID>(Ha, HLD, t.HT[0], B, r0);
-    wh.load(wt.W[2], n0);
-    train_hidden<RB>(acc, wt.b[1], n0, Z + ZL, Hb);
-    __syncthreads();
-    wh.template apply<RB>(Hb, HLD, acc);
-    store_transposed<RB, S_HID>(Hb, HLD, t.HT[1], B, r0);
-    wh.load(wt.W[3], n0);
-    train_hidden<RB>(acc, wt.b[2], n0, Z + 2 * ZL, Ha);
-    __syncthreads();
-    wh.template apply<RB>(Ha, HLD, acc);
-    store_transposed<RB, S_HID>(Ha, HLD, t.HT[2], B, r0);
+    lds_barrier();
     WTile<S_HID, 1> wo;
-    wo.load(wt.W[4], 16 * w);
-    train_hidden<RB>(acc, wt.b[3], n0, Z + 3 * ZL, Hb);
-    __syncthreads();
+#pragma unroll
+    for (int l = 1; l < 4; ++l) {   // the last leaves its result in Hb
+        uint16_t *In = (l & 1) ? Ha : Hb, *Out = (l & 1) ? Hb : Ha;
+        wh.template apply<RB>(In, HLD, acc);
+        store_transposed<RB, S_HID>(In, HLD, t.HT[l - 1], B, r0);
+        if (l < 3) wh.load(wt.W[l + 1], n0);
+        else wo.load(wt.W[4], 16 * w);
+        train_hidden<RB>(acc, wt.b[l], n0, Z + l * ZL, Out);
+        lds_barrier();
+    }
     f32x4 o[RB][1];
     wo.template apply<RB>(Hb, HLD, o);
     store_transposed<RB, S_HID>(Hb, HLD, t.HT[3], B, r0);
@@ -825,29 +862,20 @@ __global__ __launch_bounds__(256, 2) void k_mlp_train(const uint16_t *__restrict
     for (int m = 32; m > 0; m >>= 1) l2 += __shfl_xor(l2, m);
     __shared__ double sh[4];
     if (lane == 0) sh[w] = l2;
-    __syncthreads();
+    lds_barrier();
     if (tid == 0) t.lpart[blockIdx.x] += (sh[0] + sh[1]) + (sh[2] + sh[3]);
     // backward: dH = dZ W layer by layer
     w5.template apply<RB>(Xs, XLD, acc);
     store_transposed<RB, S_OUT>(Xs, XLD, t.dZ5T, B, r0);
-    wh.load(wt.WT[3], n0);
-    train_back<RB>(acc, n0, Z + 3 * ZL, r0, t.G[3], Ha);
-    __syncthreads();
-    wh.template apply<RB>(Ha, HLD, acc);
-    store_transposed<RB, S_HID>(Ha, HLD, t.dZT[3], B, r0);
-    wh.load(wt.WT[2], n0);
-    train_back<RB>(acc, n0, Z + 2 * ZL, r0, t.G[2], Hb);
-    __syncthreads();
-    wh.template apply<RB>(Hb, HLD, acc);
-    store_transposed<RB, S_HID>(Hb, HLD, t.dZT[2], B, r0);
-    wh.load(wt.WT[1], n0);
-    train_back<RB>(acc, n0, Z + ZL, r0, t.G[1], Ha);
-    __syncthreads();
-    wh.template apply<RB>(Ha, HLD, acc);
-    store_transposed<RB, S_HID>(Ha, HLD, t.dZT[1], B, r0);
-    train_back<RB>(acc, n0, Z, r0, t.G[0], Hb);
-    __syncthreads();
-    store_transposed<RB, S_HID>(Hb, HLD, t.dZT[0], B, r0);
+#pragma unroll
+    for (int l = 3; l >= 0; --l) {
+        uint16_t *Out = (l & 1) ? Ha : Hb;
+        if (l > 0) wh.load(wt.WT[l], n0);
+        train_back<RB>(acc, n0, Z + l * ZL, r0, t.G[l], Out);
+        lds_barrier();
+        if (l > 0) wh.template apply<RB>(Out, HLD, acc);
+        store_transposed<RB, S_HID>(Out, HLD, t.dZT[l], B, r0);
+    }
 }
 static constexpr size_t train_lds(int RB) { return sizeof(uint16_t) * (size_t)16 * RB * (XLD + 2 * HLD); }
 
