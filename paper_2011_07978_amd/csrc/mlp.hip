@@ -1112,7 +1112,11 @@ class PolarNormal {
     float kept = 0.0f;
     bool has = false;
     float unit() {
-        const float u = (float)rng() * 0x1p-64f;
+        // rounds as the 64-bit number does: the bit shifted out stays as a
+        // sticky one (an unsigned conversion branches on the top bit, a coin toss)
+        const uint64_t x = rng();
+        if (x < (1ull << 26)) return (float)x * 0x1p-64f;
+        const float u = (float)(int64_t)((x >> 1) | (x & 1)) * 0x1p-63f;
         return u < 1.0f ? u : 0x1.fffffep-1f;
     }
 
