@@ -18,21 +18,53 @@ __global__ void k_map_init(unsigned long long *ref_tmp, unsigned long long none)
 
 // Z_i = (beta_i - beta_ox)/(beta_f - beta_ox), beta_i = sum_k w_k Y_ik summed in
 // ascending k with separately rounded products and sums (no contraction), so
-// the candidate test Z_i < Z_tol is reproducible bit for bit.
+// the candidate test Z_i < Z_tol is reproducible bit for bit.  Bound by reading
+// Y; eight rows are on their way before the first is added, two cells a thread
+// where every row starts on 16 bytes (V = 2: an even number of cells in an
+// aligned array), one otherwise.
+template <int V>
 __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
     int64_t ncells, int N, const double *__restrict__ Y, const double *__restrict__ w,
     double beta_f, double beta_ox, double Z_tol, uint8_t *__restrict__ flags,
     unsigned long long *ref_tmp) {
+    typedef double vec __attribute__((ext_vector_type(2)));
     __shared__ unsigned long long smin[MAP_BLOCK / 64];
-    const int64_t i = (int64_t)blockIdx.x * MAP_BLOCK + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * MAP_BLOCK + threadIdx.x) * V;
     unsigned long long cand_idx = ~0ull;
-    if (i < ncells) {
-        double beta = 0.0;
-        for (int k = 0; k < N; ++k) beta = __dadd_rn(beta, __dmul_rn(w[k], Y[(int64_t)k * ncells + i]));
-        const double Z = __ddiv_rn(__dsub_rn(beta, beta_ox), __dsub_rn(beta_f, beta_ox));
-        const bool cand = Z < Z_tol;
-        flags[i] = cand ? 1 : 0;
-        if (cand) cand_idx = (unsigned long long)i;
+    if (i < ncells) {   // with V = 2 the number of cells is even
+        const double *col = Y + i;
+        double beta[V] = {};
+        auto rows = [&](const int k0, const int cnt) {
+            double y[8][V];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q >= cnt) break;
+                const double *s = col + (int64_t)(k0 + q) * ncells;
+                if constexpr (V == 2) {
+                    const vec v = *reinterpret_cast<const vec *>(s);
+                    y[q][0] = v.x;
+                    y[q][1] = v.y;
+                } else {
+                    y[q][0] = *s;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q >= cnt) break;
+#pragma unroll
+                for (int c = 0; c < V; ++c) beta[c] = __dadd_rn(beta[c], __dmul_rn(w[k0 + q], y[q][c]));
+            }
+        };
+        int k = 0;
+        for (; k + 8 <= N; k += 8) rows(k, 8);
+        for (; k < N; ++k) rows(k, 1);
+#pragma unroll
+        for (int c = V - 1; c >= 0; --c) {
+            const double Z = __ddiv_rn(__dsub_rn(beta[c], beta_ox), __dsub_rn(beta_f, beta_ox));
+            const bool cand = Z < Z_tol;
+            flags[i + c] = cand ? 1 : 0;
+            if (cand) cand_idx = (unsigned long long)(i + c);
+        }
     }
     // wave minimum, then block minimum, then one atomic per block
     unsigned long long v = cand_idx;
@@ -221,8 +253,14 @@ hipError_t launch_map(int64_t ncells, int N, const double *T, const double *Y, c
                       uint8_t *flags, unsigned long long *ref_tmp, int64_t *ref_out,
                       hipStream_t s) {
     hipLaunchKernelGGL(k_map_init, dim3(1), dim3(1), 0, s, ref_tmp, ~0ull);
-    if (ncells > 0)
-        hipLaunchKernelGGL(k_map_candidates, dim3(nblk(ncells)), dim3(MAP_BLOCK), 0, s, ncells, N, Y,
+    // two cells a thread where the rows allow it and there is a workgroup for
+    // every CU either way
+    const bool two = ncells % 2 == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ncells >= 2 * 256 * MAP_BLOCK;
+    if (two)
+        hipLaunchKernelGGL(k_map_candidates<2>, dim3(nblk(ncells / 2)), dim3(MAP_BLOCK), 0, s, ncells, N, Y,
+                           w, beta_f, beta_ox, Z_tol, flags, ref_tmp);
+    else if (ncells > 0)
+        hipLaunchKernelGGL(k_map_candidates<1>, dim3(nblk(ncells)), dim3(MAP_BLOCK), 0, s, ncells, N, Y,
                            w, beta_f, beta_ox, Z_tol, flags, ref_tmp);
     hipLaunchKernelGGL(k_map_flags, dim3(ncells > 0 ? nblk(ncells) : 1), dim3(MAP_BLOCK), 0, s,
                        ncells, T, T_tol, use_T, flags, ref_tmp, ref_out);
