@@ -105,6 +105,7 @@ struct Small {
 __host__ __device__ inline int table_doubles(const MechDev &M) {
     return M.N * SPC_STRIDE + M.R * RXN_FIELDS;
 }
+__host__ __device__ inline int slot_doubles(const MechDev &M) { return M.n * M.ldj; }
 constexpr int kLockDoubles = 8;   // slot locks (up to 16 ints) ahead of the slots
 
 // The Jacobian slot of one wavefront.  With as many slots as wavefronts
@@ -260,8 +261,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     wave_sync();
 
     // reaction pass: rates of progress scattered to the production rates of
-    // their reactant and product slots (LDS float atomics; missing slots hit
-    // the sentinel entry N)
+    // their reactant and product slots (LDS float atomics)
     const double lnp = FO ? log(p) : 0.0;
     const f64x2 *rtab = reinterpret_cast<const f64x2 *>(lds_all + N * SPC_STRIDE);
     const RxnRec *rxn = (const RxnRec *)gbl(M.rxn);
@@ -324,11 +324,13 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         }
         const double Delta = kf * Pf - kr * Pr;
         const double q = m * Delta;
+        // missing slots are guarded: most reactions lack some, and their lanes
+        // would queue on one sentinel (flame of 53 species 39.5 ms against 38.0)
         lds_add(wl + r0, -q);
-        lds_add(wl + r1, -q);
         lds_add(wl + p0, q);
-        lds_add(wl + p1, q);
-        lds_add(wl + p2, q);
+        if (r1 < N) lds_add(wl + r1, -q);
+        if (p1 < N) lds_add(wl + p1, q);
+        if (p2 < N) lds_add(wl + p2, q);
         if (JAC) {
             const double dlnkf = bj * invT + EaRj * invT * invT + dlnGdT;
             const double dH = -hl[r0] - hl[r1] + hl[p0] + hl[p1] + hl[p2];
@@ -338,26 +340,49 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
             const int sl[5] = {r0, r1, p0, p1, p2};
             const double ds[5] = {mkf * Cr1, mkf * Cr0, -mkr * Cp1 * Cp2, -mkr * Cp0 * Cp2,
                                   -mkr * Cp0 * Cp1};
+            // Slots r1, p1 and p2 may be missing (species N); each is guarded
+            // once, with the rows and columns it brings.  (A guard per atomic
+            // was half of a trip's 1000 instructions; none at all, with the
+            // missing slots adding to a row and column past the matrix, cost
+            // more in conflicts than the guards: flame of 53 species 42.4 ms
+            // against 39.8.)
+            double *cell[5];
 #pragma unroll
-            for (int a = 0; a < 5; ++a) {
-                const int sa = sl[a];
-                if (sa >= N) continue;
-                const double nu = a < 2 ? -1.0 : 1.0;
-                double *row = Jl + (sa + 1) * ldj;
-                lds_add(row, nu * dqdT);
+            for (int a = 0; a < 5; ++a) cell[a] = Jl + (sl[a] + 1) * ldj;
+            auto add = [&](const int a, const int b) { lds_add(cell[a] + 1 + sl[b], a < 2 ? -ds[b] : ds[b]); };
+            auto add_T = [&](const int a) { lds_add(cell[a], a < 2 ? -dqdT : dqdT); };
+            constexpr int R0 = 0, R1 = 1, P0 = 2, P1 = 3, P2 = 4;
+            add_T(R0); add_T(P0);
+            add(R0, R0); add(R0, P0); add(P0, R0); add(P0, P0);
+            if (r1 < N) {
+                add_T(R1);
+                add(R1, R1); add(R1, R0); add(R1, P0); add(R0, R1); add(P0, R1);
+            }
+            if (p1 < N) {
+                add_T(P1);
+                add(P1, P1); add(P1, R0); add(P1, P0); add(R0, P1); add(P0, P1);
+                if (r1 < N) { add(P1, R1); add(R1, P1); }
+            }
+            if (p2 < N) {
+                add_T(P2);
+                add(P2, P2); add(P2, R0); add(P2, P0); add(R0, P2); add(P0, P2);
+                if (r1 < N) { add(P2, R1); add(R1, P2); }
+                if (p1 < N) { add(P2, P1); add(P1, P2); }
+            }
+            if (tb != TB_NONE) {
+                const double dm = Delta * dGdM;
 #pragma unroll
-                for (int b = 0; b < 5; ++b)
-                    if (sl[b] < N) lds_add(row + 1 + sl[b], nu * ds[b]);
-                if (tb != TB_NONE) {
-                    const double nd = nu * Delta * dGdM;
-                    lds_add(tbl + sa + 1, nd);
-                    if (es0 < N) lds_add(row + 1 + es0, nd * e0v);
-                    if (es1 < N) lds_add(row + 1 + es1, nd * e1v);
-                    if (es2 < N) lds_add(row + 1 + es2, nd * e2v);
+                for (int a = 0; a < 5; ++a) {
+                    if (sl[a] >= N) continue;
+                    const double nd = a < 2 ? -dm : dm;
+                    lds_add(tbl + sl[a] + 1, nd);
+                    if (es0 < N) lds_add(cell[a] + 1 + es0, nd * e0v);
+                    if (es1 < N) lds_add(cell[a] + 1 + es1, nd * e1v);
+                    if (es2 < N) lds_add(cell[a] + 1 + es2, nd * e2v);
                     if (tb >= TB_LIST0) {
                         const int e1 = M.tb_ptr[tb - TB_LIST0 + 1];
                         for (int e = M.tb_ptr[tb - TB_LIST0]; e < e1; ++e)
-                            lds_add(row + 1 + M.eff_sp[e], nd * M.eff_am1[e]);
+                            lds_add(cell[a] + 1 + M.eff_sp[e], nd * M.eff_am1[e]);
                     }
                 }
             }
@@ -676,7 +701,7 @@ __device__ __forceinline__ bool rodas_attempt(const MechDev *__restrict__ M, dou
 template <int NP, bool LT>
 __device__ __forceinline__ double *init_lds(const MechDev *Mp, int jslots, JacSlot &js) {
     const MechDev &M = *Mp;
-    const int jd = M.n * M.ldj;
+    const int jd = slot_doubles(M);
     js.jdoubles = jd;
     js.held = -1;
     double *lds;
@@ -879,7 +904,7 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_integrate_queue(const Mech
 // Bound by the assembly's chain with one wavefront per SIMD (the slots fill the
 // LDS); copying the 27 KB table for every cell had cost as much again.  The
 // rows leave LDS as they lie, n consecutive doubles an instruction.
-template <int NP>
+template <int NP, bool FO>
 __global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
                                                                    double *fout, double *Jout) {
     JacSlot js;
@@ -892,7 +917,7 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev
         if (lane == 0) y = P.T[cell];
         else if (lane <= N) y = P.Y[(int64_t)(lane - 1) * P.ncells + cell];
         double a[NP];   // not used
-        const double f = rhs_eval<NP, RHS_JAC, true, true>(M, P.p[cell], y, lds, js.J, 0.0, a);
+        const double f = rhs_eval<NP, RHS_JAC, true, FO>(M, P.p[cell], y, lds, js.J, 0.0, a);
         if (lane < n) {
             if (fout) fout[cell * n + lane] = f;
             if (Jout) {
@@ -967,7 +992,7 @@ static WaveLayout wave_layout(const MechDev &M) {
     const int np = pick_np(M.n);
     if (np < 0) return {0, 0};
     const size_t cap = kLdsCap / sizeof(double);
-    const size_t head = (size_t)table_doubles(M) + kLockDoubles, jd = (size_t)M.n * M.ldj;
+    const size_t head = (size_t)table_doubles(M) + kLockDoubles, jd = (size_t)slot_doubles(M);
     for (int w = max_wpb(np); w >= 1; w /= 2) {
         const size_t base = head + (size_t)w * M.lds_doubles;
         if (base > cap) continue;
@@ -983,7 +1008,7 @@ int wave_kernel_wpb(const MechDev &M) { return wave_layout(M).wpb; }
 #endif
 static size_t lds_bytes(const MechDev &M, const WaveLayout &L) {
     return sizeof(double) * ((size_t)table_doubles(M) + kLockDoubles +
-                             (size_t)L.jslots * M.n * M.ldj + (size_t)L.wpb * M.lds_doubles);
+                             (size_t)L.jslots * slot_doubles(M) + (size_t)L.wpb * M.lds_doubles);
 }
 
 // Host launchers: M is the host copy (sizes), Md the device copy the kernels read.
@@ -994,7 +1019,7 @@ template <int NP, bool FO>
 static hipError_t launch_integrate_np(const MechDev &M, const MechDev *Md, const IntParams &P,
                                       int schedule, int grid, hipStream_t s) {
     if (schedule == 0) {
-        const size_t sh1 = sizeof(double) * ((size_t)M.n * M.ldj + (size_t)M.lds_doubles);
+        const size_t sh1 = sizeof(double) * ((size_t)slot_doubles(M) + (size_t)M.lds_doubles);
         hipFuncSetAttribute((const void *)k_integrate_plain<NP, FO>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh1);
         hipLaunchKernelGGL((k_integrate_plain<NP, FO>), dim3((unsigned)P.ncells), dim3(64), sh1, s, Md, P);
@@ -1068,13 +1093,13 @@ hipError_t launch_eval_rhs_jac(int NP, const MechDev &M, const MechDev *Md, cons
     const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(kLdsCap / sh, (size_t)(8 / w)));
     const int64_t need = (P.ncells + w - 1) / w;
     const unsigned grid = (unsigned)std::min<int64_t>(need, (int64_t)cus * per_cu);
-    switch (NP) {
-#define CASE(v)                                                                                 \
-    case v:                                                                                     \
-        hipFuncSetAttribute((const void *)k_eval_rhs_jac<v>,                                    \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);               \
-        hipLaunchKernelGGL(k_eval_rhs_jac<v>, dim3(grid), dim3(64 * w), sh, s, Md, P, f, J);    \
+    const auto launch = [&](void (*k)(const MechDev *, IntParams, double *, double *)) {
+        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+        hipLaunchKernelGGL(k, dim3(grid), dim3(64 * w), sh, s, Md, P, f, J);
         return hipGetLastError();
+    };
+    switch (NP) {
+#define CASE(v) case v: return M.has_fo ? launch(k_eval_rhs_jac<v, true>) : launch(k_eval_rhs_jac<v, false>);
         CHEM_NP_LIST(CASE)
 #undef CASE
     }
