@@ -133,9 +133,11 @@ __device__ __forceinline__ void block_part(double v, int i, double *red) {
     const double s = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[NW * i + (threadIdx.x >> 6)] = s;
 }
+template <int WAVES>
 __device__ __forceinline__ double block_total(int i, const double *red) {
     const double *r = red + NW * i;
-    return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
+    const double s = (r[0] + r[1]) + (r[2] + r[3]);
+    return WAVES == 4 ? s : s + ((r[4] + r[5]) + (r[6] + r[7]));
 }
 
 // NASA-7 coefficients and molar mass of a species
@@ -161,11 +163,14 @@ __device__ __forceinline__ RxnRec load_rxn(const RxnRec *__restrict__ rxn, int j
 // -----------------------------------------------------------------------------
 // f(y) and, with JAC, the analytic Jacobian into L.A (row-major, stride lda),
 // or with MAT the iteration matrix diag I - J.  Threads 2i, 2i + 1 return f_i.
-// Same formulas as the wavefront kernel.
+// Without MAT, rows 1.. of the Jacobian go straight to Jg (n x n, nullable), row
+// 0 last.  NT threads; 3 n of them map the columns.  Same formulas as the
+// wavefront kernel.
 // -----------------------------------------------------------------------------
-template <bool JAC, bool MAT>
+template <bool JAC, bool MAT, int NT>
 __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const double p, const double y,
-                                          const double diag, const BigLds &L) {
+                                          const double diag, const BigLds &L, double *__restrict__ Jg) {
+    constexpr int WAVES = NT / 64;
     // The opaque thread index and sizes keep the addresses and trip counts
     // derived from them local to this call instead of held (spilled) across
     // the step loop; so below.
@@ -187,7 +192,7 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     if (tid == 0) L.red[32] = y;
     __syncthreads();
     const double T = L.red[32];
-    const double sumYW = block_total(0, L.red);
+    const double sumYW = block_total<WAVES>(0, L.red);
     const double lnT = log(T);
     const double ln_patm_RT = kLnPatmRu - lnT;
     const double invT = recip_nr(T);
@@ -223,9 +228,9 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
         L.gi[N] = 1.0;
         if (JAC) L.hh[N] = 0.0;
     }
-    for (int i = tid; i < L.nw * (N + 1); i += BT) L.w[i] = 0.0;
+    for (int i = tid; i < L.nw * (N + 1); i += NT) L.w[i] = 0.0;
     if (JAC) {
-        for (int i = tid; i < n * lda; i += BT) L.A[i] = 0.0;
+        for (int i = tid; i < n * lda; i += NT) L.A[i] = 0.0;
         if (tid < n) L.tb[tid] = 0.0;
     }
     __syncthreads();
@@ -236,13 +241,13 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     // shared, and for the Jacobian, the wavefronts take turns, so the order of
     // every sum is fixed.
     double *wl = L.w + (size_t)(wv & (L.nw - 1)) * (N + 1);
-    const int turns = JAC ? NW : NW / L.nw;
+    const int turns = JAC ? WAVES : WAVES / L.nw;
     const int my_turn = JAC ? wv : wv / L.nw;
 #pragma unroll 1
-    for (int j0 = 0; j0 < R; j0 += BT) {
+    for (int j0 = 0; j0 < R; j0 += NT) {
         const bool valid = j0 + tid < R;
         const RxnRec rec = next;
-        if (j0 + BT < R) next = load_rxn(M.rxn, j0 + BT + tid < R ? j0 + BT + tid : R - 1);
+        if (j0 + NT < R) next = load_rxn(M.rxn, j0 + NT + tid < R ? j0 + NT + tid : R - 1);
         const int ix0 = rec.idx[0], ix1 = rec.idx[1], ix2 = rec.idx[2], ix3 = rec.idx[3];
         const int r0 = ix0 & 0xffff, r1 = (int)((unsigned)ix0 >> 16);
         const int p0 = ix1 & 0xffff, p1 = (int)((unsigned)ix1 >> 16);
@@ -351,17 +356,17 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
         if (one) L.hh[k] = fk;
     }
     __syncthreads();
-    const double hs = block_total(0, L.red);
-    const double icps = recip_nr(block_total(1, L.red));
+    const double hs = block_total<WAVES>(0, L.red);
+    const double icps = recip_nr(block_total<WAVES>(1, L.red));
     const double fT = -T * hs * icps;
     if (JAC) {
-        const double cpf = block_total(2, L.red);
-        const double dcps = block_total(3, L.red);
+        const double cpf = block_total<WAVES>(2, L.red);
+        const double dcps = block_total<WAVES>(3, L.red);
         const double Wbar = recip_nr(sumYW);
         // species rows, chain rule from concentrations to (T, Y): four threads
         // a row form its sum over the concentrations and its T column; the
         // rest of the row is an affine map per entry, x -> (W_k x + g_k) / W_c
-        for (int r = tid >> 2; r < N; r += BT / 4) {
+        for (int r = tid >> 2; r < N; r += NT / 4) {
             double *row = Jl + (r + 1) * lda;
             const double tbk = tbl[r + 1];
             double s = 0.0;
@@ -403,7 +408,8 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
                     if (i >= cnt) break;
                     if (c > 0) x[i] = iw * (wk[i] * x[i] + gk[i]);
                     acc += ek[i] * x[i];
-                    Jl[(k0 + i + 1) * lda + c] = MAT ? (k0 + i + 1 == c ? diag : 0.0) - x[i] : x[i];
+                    if (MAT) Jl[(k0 + i + 1) * lda + c] = (k0 + i + 1 == c ? diag : 0.0) - x[i];
+                    else if (Jg) Jg[(k0 + i + 1) * n + c] = x[i];
                 }
             };
             int k0 = seg * ch;
@@ -417,7 +423,8 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
             const double acc = ((gil[tid] + L.w[tid]) + tbl[tid]) * T;
             const double v = tid == 0 ? -(cpf + acc) * icps - fT * dcps * icps
                                       : -acc * icps - fT * L.cp[tid - 1] * icps;
-            Jl[tid] = MAT ? (tid == 0 ? diag : 0.0) - v : v;
+            if (MAT) Jl[tid] = (tid == 0 ? diag : 0.0) - v;
+            else if (Jg) Jg[tid] = v;
         }
         __syncthreads();
     }
@@ -738,7 +745,7 @@ __device__ __forceinline__ bool rodas_attempt_big(const MechDev *__restrict__ M,
             ys = y;
 #pragma unroll
             for (int j = 0; j < 5; ++j) ys += kBigA[s][j] * u[j];
-            rv = rhs_big<false, false>(M, p, ys, 0.0, L);
+            rv = rhs_big<false, false, BT>(M, p, ys, 0.0, L, nullptr);
 #pragma unroll
             for (int j = 0; j < 5; ++j) rv += (kBigC[s][j] * hinv) * u[j];
         }
@@ -790,7 +797,7 @@ __device__ void integrate_cell_big(const MechDev *__restrict__ M, const IntParam
         if (h >= dt - t) { h = dt - t; last = true; }
         if (h < P.hmin_frac * dt) { status = 2; break; }
         // f and the Jacobian of y, assembled as the matrix of this step size
-        const double f0 = rhs_big<true, true>(M, p, y, 1.0 / (kBigGamma * h), L);
+        const double f0 = rhs_big<true, true, BT>(M, p, y, 1.0 / (kBigGamma * h), L, nullptr);
         double ynew = 0.0, ev = 0.0;
         const bool ok = rodas_attempt_big<NR>(M, L, p, y, f0, h, ynew, ev);
         // largest scaled error; a NaN counts as infinite (both shrink by 0.2)
@@ -884,19 +891,20 @@ __global__ __launch_bounds__(BT) void k_big_queue(const MechDev *__restrict__ M,
     }
 }
 
-// Kernel-level checks: f and J per cell; one fixed Rodas4 step per cell.
-__global__ __launch_bounds__(BT) void k_big_rhs_jac(const MechDev *__restrict__ M, IntParams P,
-                                                    double *fout, double *Jout) {
+// Kernel-level checks: f and J per cell; one fixed Rodas4 step per cell.  f and J
+// need no elimination, so where three threads a column fit in 256, three
+// four-wavefront workgroups share a CU and hide one another's barriers (65
+// unknowns, 1001 cells, one eight-wavefront workgroup per CU: 70 us).
+template <int NT>
+__global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_big_rhs_jac(const MechDev *__restrict__ M, IntParams P,
+                                                                       double *fout, double *Jout) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
     const int64_t cell = blockIdx.x;
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
-    const double f = rhs_big<true, false>(M, P.p[cell], y, 0.0, L);
+    const double f = rhs_big<true, false, NT>(M, P.p[cell], y, 0.0, L, Jout ? Jout + cell * n * n : nullptr);
     if (fout && own < n && (tid & 1) == 0) fout[cell * n + own] = f;
-    if (Jout)
-        for (int i = tid; i < n * n; i += BT)
-            Jout[cell * n * n + i] = L.A[(i / n) * L.lda + (i % n)];
 }
 
 template <int NR>
@@ -908,7 +916,7 @@ __global__ __launch_bounds__(BT) void k_big_rodas_step(const MechDev *__restrict
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
     const double p = P.p[cell];
-    const double f0 = rhs_big<true, true>(M, p, y, 1.0 / (kBigGamma * h), L);
+    const double f0 = rhs_big<true, true, BT>(M, p, y, 1.0 / (kBigGamma * h), L, nullptr);
     double ynew = 0.0, err = 0.0;
     const bool ok = rodas_attempt_big<NR>(M, L, p, y, f0, h, ynew, err);
     if (!ok) { ynew = NAN; err = NAN; }
@@ -925,6 +933,9 @@ size_t big_lds_bytes(int n) { return sizeof(double) * big_lds_doubles(n); }
 // at 138).
 static int big_rows(int n) { return n <= 128 ? 2 : 3; }
 
+// Three threads a column in four wavefronts.
+static bool small_group(int n) { return 3 * n <= 256; }
+
 static hipError_t set_lds(const void *k, size_t sh) {
     return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
 }
@@ -935,7 +946,7 @@ hipError_t big_prepare(int n) {
     hipError_t e;
     if ((e = set_lds(two ? (const void *)k_big_plain<2> : (const void *)k_big_plain<3>, sh))) return e;
     if ((e = set_lds(two ? (const void *)k_big_queue<2> : (const void *)k_big_queue<3>, sh))) return e;
-    if ((e = set_lds((const void *)k_big_rhs_jac, sh))) return e;
+    if ((e = set_lds(small_group(n) ? (const void *)k_big_rhs_jac<256> : (const void *)k_big_rhs_jac<BT>, sh))) return e;
     return set_lds(two ? (const void *)k_big_rodas_step<2> : (const void *)k_big_rodas_step<3>, sh);
 }
 
@@ -958,8 +969,11 @@ hipError_t launch_integrate_big(const MechDev &M, const MechDev *Md, const IntPa
 
 hipError_t launch_big_rhs_jac(const MechDev &M, const MechDev *Md, const IntParams &P, double *f,
                               double *J, hipStream_t s) {
-    hipLaunchKernelGGL(k_big_rhs_jac, dim3((unsigned)P.ncells), dim3(BT), big_lds_bytes(M.n), s, Md,
-                       P, f, J);
+    const size_t sh = big_lds_bytes(M.n);
+    if (small_group(M.n))
+        hipLaunchKernelGGL(k_big_rhs_jac<256>, dim3((unsigned)P.ncells), dim3(256), sh, s, Md, P, f, J);
+    else
+        hipLaunchKernelGGL(k_big_rhs_jac<BT>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, f, J);
     return hipGetLastError();
 }
 
