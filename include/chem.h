@@ -10,8 +10,8 @@
  * This library is that hot path on one GPU: reference mapping, an on-device
  * work queue ordered heavy-first by the previous call's per-cell cost (the
  * analogue of the paper's CPU-time load measure), and FP64 Rosenbrock (Rodas4)
- * integration with an analytic Jacobian and batched LU, all in hand-written
- * HIP kernels.
+ * integration with an analytic Jacobian and batched Gauss-Jordan elimination,
+ * all in hand-written HIP kernels.
  *
  * Conventions for every entry point:
  *  - Array arguments marked "device" are device pointers (HIP global memory,
@@ -238,10 +238,11 @@ int chem_set_mechanism(chem_ctx *ctx, const chem_mech_desc *m);
 int chem_validate_mechanism(const chem_mech_desc *m, char *msg, int32_t msg_len);
 /* Largest species count the integrator handles: 137 (138 unknowns).  Up to
  * 63 species a wavefront integrates a cell with its iteration matrix in
- * registers; above that a workgroup of four wavefronts integrates a cell with
+ * registers; above that a workgroup of eight wavefronts integrates a cell with
  * the n x n matrix in LDS (n^2 doubles plus ~9 n, which must fit in one CU's
  * LDS: chem_set_mechanism's integrator calls return CHEM_E_UNIMPL when it does
- * not on the device at hand) and a blocked LU on the FP64 matrix cores. */
+ * not on the device at hand) and block Gauss-Jordan elimination on the FP64
+ * matrix cores. */
 int chem_max_species(void);
 
 int chem_set_options(chem_ctx *ctx, const chem_options *o);

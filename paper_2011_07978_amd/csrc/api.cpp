@@ -83,10 +83,7 @@ struct chem_ctx {
                ev5 = nullptr;
     int64_t *d_refnone = nullptr;            // device -1: "no reference cell"
     int occ = 0;
-    // large mechanisms (n > 64): workgroup-per-cell kernel, Jacobian slots of
-    // the workgroups in flight
-    bool big = false;
-    int big_slots = 0;
+    bool big = false;                        // large mechanisms (n > 64): workgroup-per-cell kernel
     bool in_capture = false, capture_failed = false;   // chem_graph_begin .. _end
     Surrogate *sur = nullptr;                // learned surrogate (null: not available)
     std::string sur_why;                     // why it is not available
@@ -218,7 +215,6 @@ static void free_mech(chem_ctx *c) {
     if (c->d_snap) (void)hipFree(c->d_snap);
     if (c->d_delta) (void)hipFree(c->d_delta);
     c->big = false;
-    c->big_slots = 0;
     c->d_mapw = c->d_snap = c->d_delta = nullptr;
     c->d_mech = nullptr;
     delete c->sur;
@@ -743,7 +739,6 @@ int chem_set_mechanism(chem_ctx *c, const chem_mech_desc *m) {
             if (occ > 0) {
                 c->big = true;
                 c->occ = occ;
-                c->big_slots = c->num_cu * occ;
             }
         }
     }
@@ -1003,8 +998,8 @@ int chem_integrate_noalloc(chem_ctx *c, int64_t n, double *T, const double *p, d
     if (n > 0 && (!T || !p || !Y)) return fail(c, CHEM_E_INVALID_ARG, "null state array");
     if (flags && !ref_index) return fail(c, CHEM_E_INVALID_ARG, "flags need ref_index");
     if (c->has_mech && c->big)
-        return fail(c, CHEM_E_UNIMPL, "chem_integrate_noalloc: mechanisms above 63 species need "
-                                      "Jacobian slots sized to the device; use chem_integrate");
+        return fail(c, CHEM_E_UNIMPL, "chem_integrate_noalloc: mechanisms above 63 species run "
+                                      "on the workgroup integrator; use chem_integrate");
     if (c->has_mech && c->N + 1 > (int)((kScrDelta - kScrSnap) / sizeof(double)))
         return fail(c, CHEM_E_UNIMPL, "chem_integrate_noalloc: too many species for the fixed workspace");
     unsigned char *base = scratch_on(c->device);

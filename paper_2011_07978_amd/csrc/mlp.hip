@@ -175,7 +175,8 @@ __device__ __forceinline__ double raw_target(const TgtSrc &t, int64_t i, int c) 
 // out + 4 c), the others targets (2 each from out + 4 nfeat).  The values take
 // longest (asinh, log: some 200 vector instructions), so 1024 threads form them,
 // and 256 add them up in LDS in the order i = t, t + 256, ... .
-// 65,536 samples, 110 columns: see the figures at train.
+// 65,536 samples, 110 columns: 135 us, beside the host's draw of the initial
+// weights; 341 us with 256 threads and a launch each for features and targets.
 constexpr int MOM_T = 1024;
 __global__ __launch_bounds__(MOM_T) void k_moments(FeatSrc f, TgtSrc t, int nfeat, double *out) {
     const int c = blockIdx.x, tid = threadIdx.x;
@@ -631,7 +632,8 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
 // of the 64 outputs of the last.  SELECTED: rows idx[0 .. *cnt) of the chunk,
 // row r's outputs to outT[c][r] as the acceptance kernel reads them; otherwise
 // all m rows from base, outputs row-major.
-// 100,003 rows: see the figures at forward_rows.
+// 100,003 rows: 166 us, bound by the GELU's vector instructions and three and a
+// bit rounds of two workgroups per CU; layer by layer through memory 505 us.
 constexpr int FT = 64;             // rows per tile
 constexpr int XLD = S_IN + 8;      // LDS row strides (bf16), padded against bank conflicts
 constexpr int HLD = S_HID + 8;
@@ -725,7 +727,7 @@ static constexpr size_t kInferLds = sizeof(uint16_t) * (size_t)FT * (XLD + 2 * H
 // pre-activations go through a scratch array laid out by thread (each thread
 // reads back what it wrote).  Layer by layer through memory, with a launch per
 // product and 2-byte transposed stores, this was 21 of an Adam step's 36
-// launches.
+// launches.  A batch of 4096: 44 us of the step's 70 (300 before).
 struct TrainBufs {
     float *Z;                              // [tile][layer][block][thread] f32x4
     uint16_t *XT, *HT[4], *dZT[4], *dZ5T;  // [column][B], operand order
