@@ -207,6 +207,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
     const double lnT = log_pos(T);
     const double ln_patm_RT = kLnPatmRu - lnT;   // ln(p_atm / (R T))
     const double invT = recip_nr(T);
+    const bool cold = T < 200.0;
     const bool sp = lane >= 1 && lane <= N;
     const int k = sp ? lane - 1 : 0;
 
@@ -249,11 +250,14 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         // species factors of the equilibrium constant: a reaction's
         // 1 / K_c = prod_products E_k / prod_reactants E_k, E_k = exp(g_k) RT / p_atm
         const double gx = gRT - ln_patm_RT;
-        gl[k] = exp_d(gx);
-        gil[k] = exp_d(-gx);
+        // Below the thermo's range (stages of a failing attempt come there) the
+        // factors could overflow against each other: their logarithms are kept.
+        gl[k] = cold ? gx : exp_d(gx);
+        gil[k] = cold ? -gx : exp_d(-gx);
         if (JAC) hl[k] = hRT;
     }
     if (lane <= N) wl[lane] = 0.0;
+    if (lane == 0) gl[N] = gil[N] = cold ? 0.0 : 1.0;   // the sentinel of missing slots
     if (JAC) {
         for (int i = lane; i < n * ldj; i += 64) Jl[i] = 0.0;
         if (lane < n) tbl[lane] = 0.0;
@@ -293,7 +297,9 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         if (FO && (tbw & TB_PLOG)) plog_arrhenius(M.plog + (size_t)j * PLOG_STRIDE, lnp, lnAj, bj, EaRj);
         const double ln_kf = lnAj + bj * lnT - EaRj * invT;
         const double kf = exp_d(ln_kf);
-        const double kr = kf * ((gl[p0] * gil[r0]) * (gl[p1] * gil[r1]) * gl[p2]);
+        double kr;
+        if (cold) kr = exp_d(ln_kf + ((gl[p0] + gil[r0]) + (gl[p1] + gil[r1]) + gl[p2]));
+        else kr = kf * ((gl[p0] * gil[r0]) * (gl[p1] * gil[r1]) * gl[p2]);
         const double Pf = Cr0 * Cr1;
         const double Pr = Cp0 * Cp1 * Cp2;
         double m = 1.0;
@@ -414,7 +420,7 @@ __device__ __forceinline__ double rhs_eval(const MechDev *__restrict__ Mp, const
         //   sum_k e_k J_kc = (sum_k H_k x_kc + sum_k e_k g_k) / W_c,  e_k = H_k / W_k,
         // so the rows stay raw in LDS, and the map is applied where they are
         // read into the matrix.  (Mapping them in LDS first cost two more
-        // passes over the slot: this part went from 12 to 7 % of an attempt.)
+        // passes over the slot.)
         double *row = Jl + (lane < n ? lane : 0) * ldj;
         double s0 = 0.0, s1 = 0.0;
         {
@@ -738,8 +744,6 @@ __device__ __forceinline__ double *init_lds(const MechDev *Mp, int jslots, JacSl
     }
     if (lane_id() == 0) {
         lds[Small<NP>::C + M.N] = 1.0;
-        lds[Small<NP>::g + M.N] = 1.0;
-        lds[Small<NP>::gi + M.N] = 1.0;
         lds[Small<NP>::h + M.N] = 0.0;
     }
     wave_sync();
@@ -902,7 +906,8 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_integrate_queue(const Mech
 // f(y) and J(y) per cell, in persistent workgroups whose wavefronts, each with a
 // private Jacobian slot, share the record table and take the cells in turn.
 // Bound by the assembly's chain with one wavefront per SIMD (the slots fill the
-// LDS); copying the 27 KB table for every cell had cost as much again.  The
+// LDS); copying the 27 KB table for every cell had cost as much again (53
+// species, 8009 cells: 441 us, now 178).  The
 // rows leave LDS as they lie, n consecutive doubles an instruction.
 template <int NP, bool FO>
 __global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
