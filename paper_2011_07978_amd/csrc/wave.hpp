@@ -118,12 +118,13 @@ __device__ __forceinline__ double recip_nr(double x) {
 }
 
 // exp(x): x = n ln 2 + r with |r| <= ln 2 / 2, exp(r) = 1 + r + r^2 q(r) with q
-// the minimax polynomial of degree 9 (relative error 3.6e-18), scaled by 2^n.
-// 19 vector instructions against about 40 of the library's; within an ulp.
-// Arguments beyond the range of doubles give 0 or infinity; NaN counts as out
-// of range (a state with a NaN is NaN through its concentrations).
+// the minimax polynomial of degree 9 (Remez exchange; relative error 3.6e-18),
+// scaled by 2^n.  19 vector instructions against about 40 of the library's;
+// within an ulp.  Results beyond the range of doubles are 0 or infinity (for
+// |x| up to 1e15).  NaN stays NaN: the power of two is clamped, not x, as fmin
+// and fmax return their other operand for a NaN.  (Rates below 0 K are NaN
+// through ln T alone: all else that enters them is finite there.)
 __device__ __forceinline__ double exp_d(double x) {
-    x = fmin(fmax(x, -1100.0), 1100.0);
     const double n = rint(x * 1.4426950408889634);
     double r = fma(-n, 0.6931471805599453, x);
     r = fma(-n, 2.3190468138462996e-17, r);
@@ -137,12 +138,12 @@ __device__ __forceinline__ double exp_d(double x) {
     q = fma(r, q, 0.16666666666666413);
     q = fma(r, q, 0.5000000000000011);
     q = fma(r, q, 1.0);
-    return ldexp(fma(r, q, 1.0), (int)n);
+    return ldexp(fma(r, q, 1.0), (int)fmin(fmax(n, -1600.0), 1600.0));
 }
 
 // log(x) for x > 0, NaN otherwise: x = 2^e m with m in [sqrt(1/2), sqrt(2)),
 // s = (m - 1) / (m + 1), log m = 2 s + s^3 P(s^2) with P the minimax
-// polynomial of degree 6 (relative error 1.2e-18).  For temperatures (e >= 5)
+// polynomial of degree 6 (Remez exchange; relative error 1.2e-18).  For temperatures (e >= 5)
 // within an ulp; near x = 1 the error is absolute, about 1e-16.
 __device__ __forceinline__ double log_pos(double x) {
     double m = __builtin_amdgcn_frexp_mant(x);
