@@ -20,7 +20,7 @@
 //     cores (v_mfma_f64_16x16x4f64);
 //   - a stage's solve is one pass over the panels (nine steps for 131
 //     unknowns) and a product with the inverted pivot blocks.
-// 8192 cells of a 130-species flame: 59.4 ms (LU by columns, triangular solves
+// 8192 cells of a 130-species flame: 58.3 ms (LU by columns, triangular solves
 // and four wavefronts: 154 ms).  Bound by the panels' chain, 1240 cycles a
 // column, 47 % of an attempted step.
 #include <hip/hip_runtime.h>
@@ -65,7 +65,7 @@ __device__ __forceinline__ void lds_add_b(double *p, double v) {
 // accesses fall into distinct banks.
 struct BigLds {
     int n, N, lda, nw;   // nw: copies of the production-rate array
-    double *A, *C, *g, *gi, *hh, *e, *cp, *tb, *w, *red;
+    double *A, *C, *g, *col, *hh, *e, *cp, *tb, *w, *red;   // col: partial column sums
     int *step, *prow;    // row -> elimination step, step -> pivot row
 };
 
@@ -97,7 +97,7 @@ __device__ __forceinline__ BigLds big_layout(int n, double *lds) {
     L.A = q; q += (size_t)n * L.lda;
     L.C = q; q += L.N + 1;
     L.g = q; q += L.N + 1;
-    L.gi = q; q += L.N + 1;
+    L.col = q; q += L.N + 1;
     L.hh = q; q += L.N + 1;
     L.e = q; q += L.N;
     L.cp = q; q += L.N;
@@ -199,7 +199,6 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     const double lnT = log(T);
     const double ln_patm_RT = kLnPatmRu - lnT;
     const double invT = recip_nr(T);
-    const bool cold = T < 200.0;
     const double pv = RU_ERG * T * sumYW;
     const double irho = pv * recip_nr(p);
     const double rho = p * recip_nr(pv);
@@ -210,26 +209,20 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
         hRT = S.a1 + T * (S.h2 + T * (S.h3 + T * (S.h4 + T * S.h5))) + S.a6 * invT;
         const double sR = S.a1 * lnT + T * (S.a2 + T * (S.s3 + T * (S.s4 + T * S.s5))) + S.a7;
         if (JAC) dcpR = S.a2 + T * (2.0 * S.a3 + T * (3.0 * S.a4 + T * (4.0 * S.a5)));
-        // species factor of the equilibrium constants on one thread of the
-        // pair, its reciprocal on the other
-        const double gx = hRT - sR - ln_patm_RT;
-        // (their logarithms below the thermo's range, as in the wavefront kernel)
-        const double ex = cold ? (half ? -gx : gx) : exp(half ? -gx : gx);
         if (half) {
-            L.gi[k] = ex;
             if (JAC) {
                 L.e[k] = hRT * S.iW;
                 L.cp[k] = cpR * S.iW;
             }
         } else {
-            L.g[k] = ex;
+            L.g[k] = hRT - sR - ln_patm_RT;
             L.C[k] = rho * yw;
             if (JAC) L.hh[k] = hRT;
         }
     }
     if (tid == 0) {   // the sentinel of missing slots
         L.C[N] = 1.0;
-        L.g[N] = L.gi[N] = cold ? 0.0 : 1.0;
+        L.g[N] = 0.0;
         if (JAC) L.hh[N] = 0.0;
     }
     for (int i = tid; i < L.nw * (N + 1); i += NT) L.w[i] = 0.0;
@@ -240,7 +233,7 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
     __syncthreads();
 
     const double lnp = M.has_fo ? log(p) : 0.0;
-    double *Cl = L.C, *gl = L.g, *gil = L.gi, *hl = L.hh, *Jl = L.A, *tbl = L.tb;
+    double *Cl = L.C, *gl = L.g, *hl = L.hh, *Jl = L.A, *tbl = L.tb;
     // Every wavefront adds to production-rate copy wv % nw; where copies are
     // shared, and for the Jacobian, the wavefronts take turns, so the order of
     // every sum is fixed.
@@ -266,9 +259,11 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
             plog_arrhenius(M.plog + (size_t)(valid ? j0 + tid : R - 1) * PLOG_STRIDE, lnp, lnAj, bj, EaRj);
         const double ln_kf = lnAj + bj * lnT - EaRj * invT;
         const double kf = exp(ln_kf);
-        double kr;
-        if (cold) kr = exp(ln_kf + ((gl[p0] + gil[r0]) + (gl[p1] + gil[r1]) + gl[p2]));
-        else kr = kf * ((gl[p0] * gil[r0]) * (gl[p1] * gil[r1]) * gl[p2]);
+        // k_r = k_f / K_c from the differences of g_k = G_k / RT - ln(p_atm / RT):
+        // exp(+-g_k) by itself leaves the range of doubles for large species at
+        // low temperatures (|g| of 700 is 1.7 MJ/mol at 300 K), and products of
+        // two of them at half of that
+        const double kr = exp(ln_kf + (((gl[p0] - gl[r0]) + (gl[p1] - gl[r1])) + gl[p2]));
         const double Pf = Cr0 * Cr1;
         const double Pr = Cp0 * Cp1 * Cp2;
         const double e0v = rec.eff[0], e1v = rec.eff[1], e2v = rec.eff[2];
@@ -393,7 +388,7 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
         // part of the temperature row sum_k e_k J_kc, and the sign
         const int seg = (tid >= n) + (tid >= 2 * n);
         const int c = tid - seg * n;
-        double *part = seg == 0 ? gil : seg == 1 ? L.w : tbl;   // free by now
+        double *part = seg == 0 ? L.col : seg == 1 ? L.w : tbl;   // free by now
         if (c < n) {
             const int ch = (N + 2) / 3;
             const int k1 = (seg + 1) * ch < N ? (seg + 1) * ch : N;
@@ -427,7 +422,7 @@ __device__ __forceinline__ double rhs_big(const MechDev *__restrict__ Mp, const 
         __syncthreads();
         // temperature row: J_T,c = -(sum_k e_k J_kc) T / cp - f_T dcp/dy_c / cp
         if (tid < n) {
-            const double acc = ((gil[tid] + L.w[tid]) + tbl[tid]) * T;
+            const double acc = ((L.col[tid] + L.w[tid]) + tbl[tid]) * T;
             const double v = tid == 0 ? -(cpf + acc) * icps - fT * dcps * icps
                                       : -acc * icps - fT * L.cp[tid - 1] * icps;
             if (MAT) Jl[tid] = (tid == 0 ? diag : 0.0) - v;
