@@ -28,6 +28,7 @@ namespace chem {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // in a caller's array
 
 __device__ __forceinline__ uint16_t f2bf(float x) {
     uint32_t u = __float_as_uint(x);
@@ -632,7 +633,8 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
 // Wavefront w computes output columns [64w, 64w + 64) of the hidden layers, 16
 // of the 64 outputs of the last.  SELECTED: rows idx[0 .. *cnt) of the chunk,
 // row r's outputs to outT[c][r] as the acceptance kernel reads them; otherwise
-// all m rows from base, outputs row-major.
+// all m rows from base, outputs row-major (of the caller's array no more than a
+// float's alignment is asked).
 // 100,003 rows: 166 us, bound by the GELU's vector instructions and three and a
 // bit rounds of two workgroups per CU; layer by layer through memory 505 us.
 constexpr int FT = 64;             // rows per tile
@@ -714,7 +716,7 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(FeatSrc f, int64_t base, i
 #pragma unroll
             for (int q = 0; q < 4; ++q) out[(size_t)(col + q) * m + r] = v[q];
         } else {
-            *(f32x4 *)(out + (size_t)(t0 + row) * S_OUT + col) = v;
+            *(f32x4_any *)(out + (size_t)(t0 + row) * S_OUT + col) = v;
         }
     }
 }
