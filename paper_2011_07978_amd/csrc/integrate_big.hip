@@ -902,7 +902,7 @@ __global__ __launch_bounds__(NT, NT == 256 ? 3 : 2) void k_big_rhs_jac(const Mec
                                                                        double *fout, double *Jout) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const int64_t cell = blockIdx.x;
+    const int64_t cell = P.first + blockIdx.x;
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
     const double f = rhs_big<true, false, NT>(M, P.p[cell], y, 0.0, L, Jout ? Jout + cell * n * n : nullptr);
@@ -914,7 +914,7 @@ __global__ __launch_bounds__(BT) void k_big_rodas_step(const MechDev *__restrict
                                                        double h, double *ynew_out, double *err_out) {
     extern __shared__ double lds[];
     const BigLds L = big_layout(M->n, lds);
-    const int64_t cell = blockIdx.x;
+    const int64_t cell = P.first + blockIdx.x;
     const int tid = threadIdx.x, own = tid >> 1, n = M->n;
     const double y = load_unknown(P, cell, M->N);
     const double p = P.p[cell];
@@ -972,20 +972,24 @@ hipError_t launch_integrate_big(const MechDev &M, const MechDev *Md, const IntPa
 hipError_t launch_big_rhs_jac(const MechDev &M, const MechDev *Md, const IntParams &P, double *f,
                               double *J, hipStream_t s) {
     const size_t sh = big_lds_bytes(M.n);
-    if (small_group(M.n))
-        hipLaunchKernelGGL(k_big_rhs_jac<256>, dim3((unsigned)P.ncells), dim3(256), sh, s, Md, P, f, J);
-    else
-        hipLaunchKernelGGL(k_big_rhs_jac<BT>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, f, J);
+    each_launch(P, [&](const IntParams &Q, unsigned cells) {
+        if (small_group(M.n))
+            hipLaunchKernelGGL(k_big_rhs_jac<256>, dim3(cells), dim3(256), sh, s, Md, Q, f, J);
+        else
+            hipLaunchKernelGGL(k_big_rhs_jac<BT>, dim3(cells), dim3(BT), sh, s, Md, Q, f, J);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_big_rodas_step(const MechDev &M, const MechDev *Md, const IntParams &P, double h,
                                  double *ynew, double *err, hipStream_t s) {
     const size_t sh = big_lds_bytes(M.n);
-    if (big_rows(M.n) == 2)
-        hipLaunchKernelGGL(k_big_rodas_step<2>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, h, ynew, err);
-    else
-        hipLaunchKernelGGL(k_big_rodas_step<3>, dim3((unsigned)P.ncells), dim3(BT), sh, s, Md, P, h, ynew, err);
+    each_launch(P, [&](const IntParams &Q, unsigned cells) {
+        if (big_rows(M.n) == 2)
+            hipLaunchKernelGGL(k_big_rodas_step<2>, dim3(cells), dim3(BT), sh, s, Md, Q, h, ynew, err);
+        else
+            hipLaunchKernelGGL(k_big_rodas_step<3>, dim3(cells), dim3(BT), sh, s, Md, Q, h, ynew, err);
+    });
     return hipGetLastError();
 }
 

@@ -149,6 +149,19 @@ struct IntParams {
     unsigned long long *stats;  // [8] device counters
     int *ref_status;        // nullable: receives the status of the reference cell (flag 1)
     int jslots;             // Jacobian slots of a queue workgroup (set by the launcher)
+    int64_t first;          // first cell of a launch with one workgroup a cell
 };
+
+// Launches with one workgroup a cell, of at most 2^22 cells each: a launch counts
+// up to 2^32 - 1 work-items a dimension, and more wrap around without an error.
+// (A loop over the cells in the kernel instead cost the evaluation of 85 unknowns
+// 30 %: values kept across the loop fill its registers.)
+template <class Launch>
+inline void each_launch(const IntParams &P, Launch launch) {
+    constexpr int64_t kCells = 1 << 22;
+    IntParams Q = P;
+    for (Q.first = 0; Q.first < P.ncells; Q.first += kCells)
+        launch(Q, (unsigned)(P.ncells - Q.first < kCells ? P.ncells - Q.first : kCells));
+}
 
 }  // namespace chem
