@@ -832,14 +832,14 @@ __device__ __forceinline__ void integrate_cell(const MechDev *__restrict__ M, co
     }
 }
 
-// Static launch: workgroup i (one wavefront) integrates cell i, reading the
+// Static launch: workgroup i (one wavefront) integrates cell first + i, reading the
 // records from global memory (an LDS copy per cell would cost more than it
 // saves).
 template <int NP, bool FO>
 __global__ __launch_bounds__(64) void k_integrate_plain(const MechDev *__restrict__ M, IntParams P) {
     JacSlot js;
     double *lds = init_lds<NP, false>(M, 0, js);
-    const int64_t cell = blockIdx.x;
+    const int64_t cell = P.first + blockIdx.x;
     if (P.flags && P.flags[cell] >= 2) return;
     integrate_cell<NP, false, FO>(M, P, cell, lds, js);
 }
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(64) void k_rodas_step(const MechDev *__restrict__ M
                                                    double h, double *ynew_out, double *err_out) {
     JacSlot js;
     double *lds = init_lds<NP, true>(M, 0, js);
-    const int64_t cell = blockIdx.x;
+    const int64_t cell = P.first + blockIdx.x;
     const int lane = lane_id(), n = M->n, N = M->N;
     double y = 0.0;
     if (lane == 0) y = P.T[cell];
@@ -1027,7 +1027,9 @@ static hipError_t launch_integrate_np(const MechDev &M, const MechDev *Md, const
         const size_t sh1 = sizeof(double) * ((size_t)slot_doubles(M) + (size_t)M.lds_doubles);
         hipFuncSetAttribute((const void *)k_integrate_plain<NP, FO>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh1);
-        hipLaunchKernelGGL((k_integrate_plain<NP, FO>), dim3((unsigned)P.ncells), dim3(64), sh1, s, Md, P);
+        each_launch(P, [&](const IntParams &Q, unsigned cells) {
+            hipLaunchKernelGGL((k_integrate_plain<NP, FO>), dim3(cells), dim3(64), sh1, s, Md, Q);
+        });
     } else {
         const WaveLayout L = wave_layout(M);
         if (L.wpb == 0 || L.jslots > 2 * kLockDoubles) return hipErrorInvalidConfiguration;
@@ -1119,7 +1121,9 @@ hipError_t launch_rodas_step(int NP, const MechDev &M, const MechDev *Md, const 
     case v:                                                                                     \
         hipFuncSetAttribute((const void *)k_rodas_step<v>,                                      \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);               \
-        hipLaunchKernelGGL(k_rodas_step<v>, dim3((unsigned)P.ncells), dim3(64), sh, s, Md, P, h, ynew, err); \
+        each_launch(P, [&](const IntParams &Q, unsigned cells) {                                \
+            hipLaunchKernelGGL(k_rodas_step<v>, dim3(cells), dim3(64), sh, s, Md, Q, h, ynew, err); \
+        });                                                                                     \
         return hipGetLastError();
         CHEM_NP_LIST(CASE)
 #undef CASE
