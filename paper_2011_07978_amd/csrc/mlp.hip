@@ -1187,7 +1187,11 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
     if (n < B) { snprintf(err, 256, "fewer samples than one batch"); return -1; }
     int rc = reserve_ws(B, true, err);
     if (rc) return rc;
-    // per-call buffers, released on every return
+    // Host arrays that copies read, then per-call buffers, released on every
+    // return: the buffers go first, and freeing them waits for the device, so no
+    // copy outlives its source when a later allocation or launch fails.
+    std::vector<float> h(weights_count(), 0.0f);
+    std::vector<int> perm;
     struct Bufs {
         std::vector<void *> v;
         ~Bufs() { for (void *p : v) (void)hipFree(p); }
@@ -1199,7 +1203,6 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
     SCHK(hipGetLastError());
     // He-style initialisation (seeded), zero biases, small output layer, drawn
     // while the device forms the moments
-    std::vector<float> h(weights_count(), 0.0f);
     {
         PolarNormal nd(seed);
         for (int l = 0; l < 5; ++l) {
@@ -1239,7 +1242,7 @@ int Surrogate::train(const FeatSrc &f, const TgtSrc &t, int epochs, int B, doubl
     if (all_rows)
         hipLaunchKernelGGL(k_build_rows, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, f, t, (const int *)nullptr,
                            n, P + weights_count(), Xall, Tall);
-    std::vector<int> perm(n);
+    perm.resize(n);
     std::mt19937_64 rng(seed ^ 0x9e3779b97f4a7c15ull);
     auto shuffle = [&] {
         std::iota(perm.begin(), perm.end(), 0);
