@@ -904,10 +904,14 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_integrate_queue(const Mech
 }
 
 // f(y) and J(y) per cell, in persistent workgroups whose wavefronts, each with a
-// private Jacobian slot, share the record table and take the cells in turn.
+// private Jacobian slot, share the record table.  Cells go to the workgroups
+// first and to their wavefronts second, so that a call of up to one cell per CU
+// has one wavefront working on each (its workgroup's others only help to copy the
+// table); packed into as few workgroups as hold them, the wavefronts of one CU
+// waited for each other's LDS atomics.
 // Bound by the assembly's chain with one wavefront per SIMD (the slots fill the
 // LDS); copying the 27 KB table for every cell had cost as much again (53
-// species, 8009 cells: 441 us, now 178).  The
+// species, 8009 cells: 441 us, now 157; 256 cells 28 us, packed 29, now 17).  The
 // rows leave LDS as they lie, n consecutive doubles an instruction.
 template <int NP, bool FO>
 __global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev *__restrict__ M, IntParams P,
@@ -916,7 +920,7 @@ __global__ __launch_bounds__(64 * max_wpb(NP)) void k_eval_rhs_jac(const MechDev
     double *lds = init_lds<NP, true>(M, 0, js);
     const int lane = lane_id(), n = M->n, N = M->N, ldj = M->ldj;
     const int wpb = (int)(blockDim.x >> 6);
-    for (int64_t cell = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); cell < P.ncells;
+    for (int64_t cell = blockIdx.x + (int64_t)gridDim.x * uniform_i(threadIdx.x >> 6); cell < P.ncells;
          cell += (int64_t)gridDim.x * wpb) {
         double y = 0.0;
         if (lane == 0) y = P.T[cell];
@@ -1088,7 +1092,7 @@ hipError_t launch_integrate_fo(int NP, const MechDev &M, const MechDev *Md, cons
 
 hipError_t launch_eval_rhs_jac(int NP, const MechDev &M, const MechDev *Md, const IntParams &P,
                                double *f, double *J, hipStream_t s) {
-    // as many wavefronts as have room for a slot each, one workgroup per CU
+    // as many wavefronts as have room for a slot each
     int w = max_wpb(NP);
     while (w > 1 && lds_bytes(M, WaveLayout{w, w}) > kLdsCap) --w;
     const size_t sh = lds_bytes(M, WaveLayout{w, w});
@@ -1097,12 +1101,17 @@ hipError_t launch_eval_rhs_jac(int NP, const MechDev &M, const MechDev *Md, cons
     if ((e = hipGetDevice(&dev)) ||
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))
         return e;
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(kLdsCap / sh, (size_t)(8 / w)));
-    const int64_t need = (P.ncells + w - 1) / w;
-    const unsigned grid = (unsigned)std::min<int64_t>(need, (int64_t)cus * per_cu);
     const auto launch = [&](void (*k)(const MechDev *, IntParams, double *, double *)) {
         hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-        hipLaunchKernelGGL(k, dim3(grid), dim3(64 * w), sh, s, Md, P, f, J);
+        // a workgroup per CU, and where those have a cell for every wavefront
+        // as many as are resident together
+        int64_t grid = std::min<int64_t>(P.ncells, cus);
+        if (P.ncells > (int64_t)cus * w) {
+            int per_cu = 0;
+            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64 * w, sh))) return e;
+            grid = std::min<int64_t>((P.ncells + w - 1) / w, (int64_t)cus * std::max(1, per_cu));
+        }
+        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * w), sh, s, Md, P, f, J);
         return hipGetLastError();
     };
     switch (NP) {
