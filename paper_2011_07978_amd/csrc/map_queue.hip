@@ -19,10 +19,12 @@ __global__ void k_map_init(unsigned long long *ref_tmp, unsigned long long none)
 // Z_i = (beta_i - beta_ox)/(beta_f - beta_ox), beta_i = sum_k w_k Y_ik summed in
 // ascending k with separately rounded products and sums (no contraction), so
 // the candidate test Z_i < Z_tol is reproducible bit for bit.  Bound by reading
-// Y; eight rows are on their way before the first is added, two cells a thread
-// where every row starts on 16 bytes (V = 2: an even number of cells in an
-// aligned array), one otherwise.
-template <int V>
+// Y: D rows are on their way before the first is added (launch_map), two cells a
+// thread where every row starts on 16 bytes (V = 2: an even number of cells in
+// an aligned array), one otherwise.  1,048,576 cells of 53 species 71 us without
+// and 73 us with 60 % candidates (6.2 TB/s); one row in flight and one cell a
+// thread 74 and 108, eight and two 97 and 98.
+template <int V, int D>
 __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
     int64_t ncells, int N, const double *__restrict__ Y, const double *__restrict__ w,
     double beta_f, double beta_ox, double Z_tol, uint8_t *__restrict__ flags,
@@ -35,9 +37,9 @@ __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
         const double *col = Y + i;
         double beta[V] = {};
         auto rows = [&](const int k0, const int cnt) {
-            double y[8][V];
+            double y[D][V];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
+            for (int q = 0; q < D; ++q) {
                 if (q >= cnt) break;
                 const double *s = col + (int64_t)(k0 + q) * ncells;
                 if constexpr (V == 2) {
@@ -49,14 +51,16 @@ __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
                 }
             }
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
+            for (int q = 0; q < D; ++q) {
                 if (q >= cnt) break;
 #pragma unroll
                 for (int c = 0; c < V; ++c) beta[c] = __dadd_rn(beta[c], __dmul_rn(w[k0 + q], y[q][c]));
             }
         };
         int k = 0;
-        for (; k + 8 <= N; k += 8) rows(k, 8);
+#pragma unroll 1
+        for (; k + D <= N; k += D) rows(k, D);
+#pragma unroll 1
         for (; k < N; ++k) rows(k, 1);
 #pragma unroll
         for (int c = V - 1; c >= 0; --c) {
@@ -66,7 +70,10 @@ __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
             if (cand) cand_idx = (unsigned long long)(i + c);
         }
     }
-    // wave minimum, then block minimum, then one atomic per block
+    // wave minimum, then block minimum, then one atomic per block.  They queue at
+    // one address, some 8 ns each (24 us of the 1 M cells above), so from 512
+    // blocks on a block first looks whether its index is still below the minimum,
+    // which only falls; in a smaller grid that look costs more than the queue.
     unsigned long long v = cand_idx;
     for (int m = 1; m < 64; m <<= 1) {
         unsigned lo = __shfl_xor((unsigned)(v & 0xffffffffu), m);
@@ -79,7 +86,10 @@ __global__ __launch_bounds__(MAP_BLOCK) void k_map_candidates(
     if (threadIdx.x == 0) {
         unsigned long long b = smin[0];
         for (int q = 1; q < MAP_BLOCK / 64; ++q) b = smin[q] < b ? smin[q] : b;
-        if (b != ~0ull) atomicMin(ref_tmp, b);
+        if (b != ~0ull &&
+            (gridDim.x <= 512 ||
+             b < __hip_atomic_load(ref_tmp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+            atomicMin(ref_tmp, b);
     }
 }
 
@@ -253,15 +263,24 @@ hipError_t launch_map(int64_t ncells, int N, const double *T, const double *Y, c
                       uint8_t *flags, unsigned long long *ref_tmp, int64_t *ref_out,
                       hipStream_t s) {
     hipLaunchKernelGGL(k_map_init, dim3(1), dim3(1), 0, s, ref_tmp, ~0ull);
-    // two cells a thread where the rows allow it and there is a workgroup for
-    // every CU either way
-    const bool two = ncells % 2 == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ncells >= 2 * 256 * MAP_BLOCK;
-    if (two)
-        hipLaunchKernelGGL(k_map_candidates<2>, dim3(nblk(ncells / 2)), dim3(MAP_BLOCK), 0, s, ncells, N, Y,
-                           w, beta_f, beta_ox, Z_tol, flags, ref_tmp);
-    else if (ncells > 0)
-        hipLaunchKernelGGL(k_map_candidates<1>, dim3(nblk(ncells)), dim3(MAP_BLOCK), 0, s, ncells, N, Y,
-                           w, beta_f, beta_ox, Z_tol, flags, ref_tmp);
+    // Two cells a thread where the rows allow it and there is a workgroup for
+    // every CU either way.  Rows in flight per thread: what keeps about 4 MB on
+    // their way together (ncells x D x 8 bytes; latency times bandwidth), which
+    // one row does from half a million cells on.  More only hurts there, and most
+    // where the rows lie a power of two apart and share their memory channels: 1 M
+    // cells of 53 species 71 us with one row, 97 with eight.  Fewer cells need
+    // more: 131,072 cells 18 us with one row, 11 with four.  Rows of an odd number
+    // of cells never share channels, and two are the faster there (1 M cells, 60 %
+    // candidates, 76 us against 85).
+    if (ncells > 0) {
+        const bool two = ncells % 2 == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0 && ncells >= 1 << 17;
+        const int d = ncells < 1 << 17 ? 8 : ncells < 1 << 18 ? 4 : ncells < 1 << 19 || ncells % 2 ? 2 : 1;
+        const auto k = two ? (d == 4 ? k_map_candidates<2, 4> : d == 2 ? k_map_candidates<2, 2> : k_map_candidates<2, 1>)
+                           : (d == 8 ? k_map_candidates<1, 8> : d == 4 ? k_map_candidates<1, 4>
+                              : d == 2 ? k_map_candidates<1, 2> : k_map_candidates<1, 1>);
+        hipLaunchKernelGGL(k, dim3(nblk(two ? ncells / 2 : ncells)), dim3(MAP_BLOCK), 0, s, ncells, N, Y, w,
+                           beta_f, beta_ox, Z_tol, flags, ref_tmp);
+    }
     hipLaunchKernelGGL(k_map_flags, dim3(ncells > 0 ? nblk(ncells) : 1), dim3(MAP_BLOCK), 0, s,
                        ncells, T, T_tol, use_T, flags, ref_tmp, ref_out);
     return hipGetLastError();
