@@ -628,7 +628,7 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
     if (sel) idx[off + __popcll(b & ((1ull << lane) - 1ull))] = r;
 }
 
-// The whole network for a tile of 64 rows in one workgroup: the input tile and
+// The whole network for a tile of 16 RB rows in one workgroup: the input tile and
 // the hidden activations stay in LDS (bf16), weights stream from L2.
 // Wavefront w computes output columns [64w, 64w + 64) of the hidden layers, 16
 // of the 64 outputs of the last.  SELECTED: rows idx[0 .. *cnt) of the chunk,
@@ -637,7 +637,11 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
 // float's alignment is asked).
 // 100,003 rows: 166 us, bound by the GELU's vector instructions and three and a
 // bit rounds of two workgroups per CU; layer by layer through memory 505 us.
-constexpr int FT = 64;             // rows per tile
+// A call of at most 16 rows per CU (narrow_tiles) takes tiles of 16 rows: each
+// lane then has a quarter of the GELUs behind one another, which is most of a
+// tile's time (one row 11 us against 28, 4096 rows 16 against 37).
+constexpr int FT = 64;             // rows per tile of a large call, and of selected rows
+static bool narrow_tiles(int64_t rows) { return rows <= 16 * 256; }
 constexpr int XLD = S_IN + 8;      // LDS row strides (bf16), padded against bank conflicts
 constexpr int HLD = S_HID + 8;
 struct MlpW {
@@ -660,54 +664,56 @@ __device__ __forceinline__ void gelu_tile(const f32x4 (&acc)[RB][4], const float
     }
 }
 
-template <bool SELECTED>
+template <bool SELECTED, int RB>
 __global__ __launch_bounds__(256, 2) void k_mlp_infer(FeatSrc f, int64_t base, int m, const int *idx,
                                                       const int *cnt, const float *norm, MlpW wt,
                                                       float *out) {
+    constexpr int R = 16 * RB;
     extern __shared__ __align__(16) uint16_t sm16[];
-    uint16_t *Xs = sm16, *Ha = Xs + FT * XLD, *Hb = Ha + FT * HLD;
+    uint16_t *Xs = sm16, *Ha = Xs + R * XLD, *Hb = Ha + R * HLD;
     const int n_sel = SELECTED ? *cnt : m;
-    const int t0 = blockIdx.x * FT;
+    const int t0 = blockIdx.x * R;
     if (t0 >= n_sel) return;                       // whole workgroup
-    const int rows = n_sel - t0 < FT ? n_sel - t0 : FT;
+    const int rows = n_sel - t0 < R ? n_sel - t0 : R;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n0 = 64 * w;
     WTile<S_IN, 4> w0;
     w0.load(wt.W[0], n0);
     {
-        // lane = row, so that each feature of a tile is one coalesced read
-        const int nfeat = f.N + 3;
-        const int64_t i = base + (SELECTED ? idx[t0 + (lane < rows ? lane : 0)] : t0 + (lane < rows ? lane : 0));
+        // neighbouring lanes on neighbouring rows, so that each feature of a tile
+        // is one coalesced read
+        const int nfeat = f.N + 3, q = tid % R;
+        const int64_t i = base + (SELECTED ? idx[t0 + (q < rows ? q : 0)] : t0 + (q < rows ? q : 0));
 #pragma unroll 4
-        for (int c = w; c < S_IN; c += 4) {
+        for (int c = tid / R; c < S_IN; c += 256 / R) {
             uint16_t v = 0;
-            if (lane < rows && c < nfeat) v = f2bf((float)((raw_feature(f, i, c) - norm[c]) / norm[64 + c]));
-            Xs[lane * XLD + c] = v;
+            if (q < rows && c < nfeat) v = f2bf((float)((raw_feature(f, i, c) - norm[c]) / norm[64 + c]));
+            Xs[q * XLD + c] = v;
         }
     }
     lds_barrier();
-    f32x4 acc[4][4];
-    w0.apply<4>(Xs, XLD, acc);
+    f32x4 acc[RB][4];
+    w0.template apply<RB>(Xs, XLD, acc);
     WTile<S_HID, 4> wh;
     WTile<S_HID, 1> wo;
     wh.load(wt.W[1], n0);
-    gelu_tile<4>(acc, wt.b[0], n0, Ha);
+    gelu_tile<RB>(acc, wt.b[0], n0, Ha);
     lds_barrier();
 #pragma unroll
     for (int l = 1; l < 4; ++l) {   // the last leaves its result in Hb
         uint16_t *In = (l & 1) ? Ha : Hb, *Out = (l & 1) ? Hb : Ha;
-        wh.apply<4>(In, HLD, acc);
+        wh.template apply<RB>(In, HLD, acc);
         if (l < 3) wh.load(wt.W[l + 1], n0);
         else wo.load(wt.W[4], 16 * w);
-        gelu_tile<4>(acc, wt.b[l], n0, Out);
+        gelu_tile<RB>(acc, wt.b[l], n0, Out);
         lds_barrier();
     }
-    f32x4 o[4][1];
-    wo.apply<4>(Hb, HLD, o);
+    f32x4 o[RB][1];
+    wo.template apply<RB>(Hb, HLD, o);
     const int col = 16 * w + 4 * (lane >> 4);
     const f32x4 bc = *(const f32x4 *)(wt.b[4] + col);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RB; ++i) {
         const int row = 16 * i + (lane & 15);
         if (row >= rows) continue;
         const f32x4 v = o[i][0] + bc;
@@ -720,7 +726,8 @@ __global__ __launch_bounds__(256, 2) void k_mlp_infer(FeatSrc f, int64_t base, i
         }
     }
 }
-static constexpr size_t kInferLds = sizeof(uint16_t) * (size_t)FT * (XLD + 2 * HLD);
+static constexpr size_t infer_lds(int rows) { return sizeof(uint16_t) * (size_t)rows * (XLD + 2 * HLD); }
+static constexpr size_t kInferLds = infer_lds(FT);
 
 // ------------------------------------------------------- training: a tile ----
 // Forward and backward of 16 RB rows of the batch in one workgroup.  The tile's
@@ -951,9 +958,9 @@ Surrogate::~Surrogate() {
 int Surrogate::init(int N_, int nel_, const std::vector<double> &E_host, char *err) {
     N = N_;
     nel = nel_;
-    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)kInferLds));
-    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    SCHK(hipFuncSetAttribute((const void *)k_mlp_infer<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)kInferLds));
     SCHK(hipFuncSetAttribute((const void *)k_mlp_train<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)train_lds(2)));
@@ -1332,9 +1339,10 @@ int Surrogate::forward_rows(const FeatSrc &f, float *out_dev, hipStream_t s, cha
     const int chunk = 1 << 24;
     for (int64_t base = 0; base < n; base += chunk) {
         const int m = (int)std::min<int64_t>(chunk, n - base);
-        hipLaunchKernelGGL(k_mlp_infer<false>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
-                           (const int *)nullptr, (const int *)nullptr, P + weights_count(), infer_weights(),
-                           out_dev + base * S_OUT);
+        const int rows = narrow_tiles(n) ? 16 : FT;
+        hipLaunchKernelGGL((rows == 16 ? k_mlp_infer<false, 1> : k_mlp_infer<false, 4>), dim3((m + rows - 1) / rows),
+                           dim3(256), infer_lds(rows), s, f, base, m, (const int *)nullptr, (const int *)nullptr,
+                           P + weights_count(), infer_weights(), out_dev + base * S_OUT);
     }
     SCHK(hipGetLastError());
     return 0;
@@ -1351,7 +1359,7 @@ int Surrogate::forward_fused_rows(const FeatSrc &f, float *out_dev, hipStream_t 
     for (int64_t base = 0; base < n; base += chunk) {
         const int m = (int)std::min<int64_t>(chunk, n - base);
         hipLaunchKernelGGL(k_select_all, dim3((m + 255) / 256), dim3(256), 0, s, m, idx, sel_cnt);
-        hipLaunchKernelGGL(k_mlp_infer<true>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
+        hipLaunchKernelGGL((k_mlp_infer<true, 4>), dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
                            idx, sel_cnt, P + weights_count(), wts, out);
         hipLaunchKernelGGL(k_untranspose, dim3((unsigned)(((int64_t)m * S_OUT + 255) / 256)), dim3(256),
                            0, s, out, m, out_dev + base * S_OUT);
@@ -1378,7 +1386,7 @@ int Surrogate::apply(const FeatSrc &f, double *T, double *Y, uint8_t *flags, con
         hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, sel_cnt);
         hipLaunchKernelGGL(k_sur_select, dim3((m + 255) / 256), dim3(256), 0, s, flags, T, base, m,
                            pin.T_max, idx, sel_cnt);
-        hipLaunchKernelGGL(k_mlp_infer<true>, dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
+        hipLaunchKernelGGL((k_mlp_infer<true, 4>), dim3((m + FT - 1) / FT), dim3(256), kInferLds, s, f, base, m,
                            idx, sel_cnt, P + weights_count(), wts, out);
         launch_post(nel, dim3((m + 255) / 256), s, f, base, m, out, q, T, Y, flags, stats);
     }

@@ -77,3 +77,22 @@ def test_forward_past_its_chunk():
     whole = n // kinds * kinds
     assert (out[:whole].view(-1, kinds, 64) == first).all()
     assert (out[whole:] == first[:n - whole]).all()
+
+
+def test_narrow_and_wide_tiles_agree():
+    """Calls of up to 4096 rows run in tiles of 16 rows, larger ones in tiles of
+    64: the same bits for every row, at ragged ends too."""
+    from tests.gpu_util import chem_for, dev, say
+    mech = synth.mechanism("mech53")
+    c = chem_for(mech)
+    c.surrogate_set_params(_params(mech.n_species, 71))
+    f = synth.subsample(synth.field_mapped(20000, seed=72), np.arange(5003))
+    dt = synth.surrogate_dt(5003, 73)
+
+    def forward(lo, hi):
+        return c.surrogate_forward(dev(f.T[lo:hi]), dev(f.p[lo:hi]), dev(f.Y[:, lo:hi]), dev(dt[lo:hi]))
+
+    say("tile widths")
+    narrow = torch.cat([forward(0, 1), forward(1, 16), forward(16, 33), forward(33, 4096), forward(4096, 5003)])
+    for n in (4095, 4096, 4097, 4160, 5003):
+        assert torch.equal(forward(0, n), narrow[:n]), n
