@@ -349,14 +349,15 @@ int chem_surrogate_set_params(chem_ctx *ctx, const float *host);
 int chem_surrogate_save(chem_ctx *ctx, const char *path);
 int chem_surrogate_load(chem_ctx *ctx, const char *path);
 /* Raw network outputs (normalised) for n cells: out [n][64] float32 device,
- * row-major.  dt [n] device.  Kernel-level check of inference. */
+ * row-major, of no more than a float's alignment.  dt [n] device.  One kernel
+ * runs the whole network per tile of 16 or 64 rows in one workgroup, activations
+ * kept in LDS. */
 int chem_surrogate_forward(chem_ctx *ctx, int64_t n, const double *T, const double *p,
                            const double *Y, const double *dt, float *out);
-/* The same outputs from the fused inference kernel that
- * chem_integrate_surrogate runs (the whole network per tile of 64 rows in one
- * workgroup, activations kept in LDS), every row selected: same arguments and
- * layout as chem_surrogate_forward.  Its products accumulate in the same
- * order, so the two entry points agree bit for bit; kernel-level check. */
+/* The same outputs the way chem_integrate_surrogate runs the kernel: the rows of
+ * a chunk from a list (here every row), outputs column by column as the gate
+ * reads them, turned back into rows.  Same arguments, layout and bits as
+ * chem_surrogate_forward; kernel-level check of that launch. */
 int chem_surrogate_forward_fused(chem_ctx *ctx, int64_t n, const double *T, const double *p,
                                  const double *Y, const double *dt, float *out);
 /* Mean-squared-error loss and its gradient (host, float32, blob layout, the

@@ -635,8 +635,9 @@ __global__ __launch_bounds__(256) void k_sur_select(const uint8_t *flags, const 
 // row r's outputs to outT[c][r] as the acceptance kernel reads them; otherwise
 // all m rows from base, outputs row-major (of the caller's array no more than a
 // float's alignment is asked).
-// 100,003 rows: 166 us, bound by the GELU's vector instructions and three and a
-// bit rounds of two workgroups per CU; layer by layer through memory 505 us.
+// 100,003 rows: 150 us a call (167 in a kernel trace, at lower clocks), bound by
+// the GELU's vector instructions and three and a bit rounds of two workgroups per
+// CU; layer by layer through memory 505 us.
 // A call of at most 16 rows per CU (narrow_tiles) takes tiles of 16 rows: each
 // lane then has a quarter of the GELUs behind one another, which is most of a
 // tile's time (one row 11 us against 28, 4096 rows 16 against 37).
