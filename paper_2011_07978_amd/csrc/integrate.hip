@@ -1092,26 +1092,33 @@ hipError_t launch_integrate_fo(int NP, const MechDev &M, const MechDev *Md, cons
 
 hipError_t launch_eval_rhs_jac(int NP, const MechDev &M, const MechDev *Md, const IntParams &P,
                                double *f, double *J, hipStream_t s) {
-    // as many wavefronts as have room for a slot each
-    int w = max_wpb(NP);
-    while (w > 1 && lds_bytes(M, WaveLayout{w, w}) > kLdsCap) --w;
-    const size_t sh = lds_bytes(M, WaveLayout{w, w});
     int dev = 0, cus = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) ||
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))
         return e;
+    const auto bytes = [&](int w) { return lds_bytes(M, WaveLayout{w, w}); };
+    // as many wavefronts as have room for a slot each
+    int w = max_wpb(NP);
+    while (w > 1 && bytes(w) > kLdsCap) --w;
     const auto launch = [&](void (*k)(const MechDev *, IntParams, double *, double *)) {
-        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes(w));
         // a workgroup per CU, and where those have a cell for every wavefront
-        // as many as are resident together
+        // as many as are resident together; of eight and four wavefronts a
+        // workgroup the one that leaves more resident (registers allow the
+        // small mechanisms twelve a CU: 10 species, 200,000 cells 478 us with
+        // eight, 414 with four)
         int64_t grid = std::min<int64_t>(P.ncells, cus);
         if (P.ncells > (int64_t)cus * w) {
-            int per_cu = 0;
-            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64 * w, sh))) return e;
+            int per_cu = 0, per_cu4 = 0;
+            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64 * w, bytes(w)))) return e;
+            if (w == 8) {
+                if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu4, k, 64 * 4, bytes(4)))) return e;
+                if (4 * per_cu4 > 8 * per_cu) w = 4, per_cu = per_cu4;
+            }
             grid = std::min<int64_t>((P.ncells + w - 1) / w, (int64_t)cus * std::max(1, per_cu));
         }
-        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * w), sh, s, Md, P, f, J);
+        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * w), bytes(w), s, Md, P, f, J);
         return hipGetLastError();
     };
     switch (NP) {
